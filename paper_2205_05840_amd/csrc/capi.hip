@@ -21,6 +21,7 @@
 #include "../../include/ndmg.h"
 #include "generic.hpp"
 #include "kernels.hpp"
+#include "small.hpp"
 #include "tuning.hpp"
 #include "ndmg_internal.hpp"
 
@@ -103,6 +104,7 @@ struct Cls {
   size_t o_tw = 0, o_tb = 0;       // time stepping: predictor and right-hand side (FP64, per pair)
   size_t o_alpha0 = 0;             // zeros: alpha = 0 turns the operator into the mass matrix
   size_t o_coef = 0;               // coefficient boxes (r^3 doubles), if any
+  size_t o_tab = 0;                // tables of the small-level kernels
 };
 
 struct Plan {
@@ -412,6 +414,7 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
   C.o_tb = take(v8);
   C.o_alpha0 = take(np * sizeof(double));
   if (cf.r > 0) C.o_coef = take(pl.coef.size() * sizeof(double));
+  C.o_tab = take((size_t)ndmg::kSmallWords * sizeof(uint32_t));
   return NDMG_OK;
 }
 
@@ -518,6 +521,21 @@ ndmg::DSub level_dsub(ndmg_ctx* c, const LevelHost& L) {
   d.nchunks = (int)(L.chunks.size() / 4);
   d.bofs = at<int64_t>(c, L.o_bofs);
   return d;
+}
+
+template <typename T>
+ndmg::SmallSub<T> small_sub(ndmg_ctx* c, const Cls& C, const LevelHost& L) {
+  return ndmg::SmallSub<T>{ndmg::dgeom(L.g),
+                           L.g.h,
+                           L.sub.nH,
+                           at<uint32_t>(c, C.o_tab),
+                           at<T>(c, L.o_ATinv),
+                           at<T>(c, L.o_XT),
+                           at<T>(c, L.o_Sinv),
+                           (int64_t)L.blk_Sinv,
+                           at<T>(c, L.o_Y),
+                           at<T>(c, L.o_r),
+                           c->plan.opts.eta};
 }
 
 // All pairs of a class, or only its active ones.
@@ -862,6 +880,7 @@ int build_class_factors(ndmg_ctx* c, Cls& C, Staging& stg) {
   }
   NDMG_TRY(stg.put_vec(c, C.o_alpha, C.alpha));
   if (!pl.coef.empty()) NDMG_TRY(stg.put_vec(c, C.o_coef, pl.coef));
+  NDMG_TRY(stg.put_vec(c, C.o_tab, ndmg::small_tables()));
   return NDMG_OK;
 }
 
@@ -930,6 +949,26 @@ int vcycle_rec(ndmg_ctx* c, Cls& C, int k, const T* g, T* z, const ndmg::Bat& bt
   const int m = pl.opts.m;
   auto P = level_ptrs<T>(c, L);
   LevelHost& Lc = C.lv[k - 1];
+  const T* none = nullptr;
+  T* zc = at<T>(c, Lc.o_z);
+  // (the launches of a batch's other size classes share the device with this one's)
+  if (!L.gen && ndmg::small_level(L.sub.nH, std::max(bt.count, pl.npairs))) {
+    // the same steps, with the residual, the condensation, the prolongation and the patch
+    // products in one launch, and the residual in the restriction's
+    const ndmg::SmallSub<T> S = small_sub<T>(c, C, L);
+    const ndmg::DGeom gc = ndmg::dgeom(Lc.g);
+    for (int l = 0; l < m; ++l) {
+      NDMG_HIP(ndmg::launch_small_patch<T>(l ? 1 : 0, g, z, none, S, gc, bt, st));
+      NDMG_HIP(ndmg::launch_small_pull<T>(l ? P.r : g, z, none, l == 0, S, gc, bt, st));
+    }
+    NDMG_HIP(ndmg::launch_small_restrict<T>(g, z, at<T>(c, Lc.o_g), ndmg::dgeom(L.g), L.g.h, gc, bt, st));
+    NDMG_TRY(vcycle_rec<T>(c, C, k - 1, at<T>(c, Lc.o_g), zc, bt, st));
+    for (int l = 0; l < m; ++l) {
+      NDMG_HIP(ndmg::launch_small_patch<T>(l ? 1 : 2, g, z, l ? none : zc, S, gc, bt, st));
+      NDMG_HIP(ndmg::launch_small_pull<T>(P.r, z, l ? none : zc, 0, S, gc, bt, st));
+    }
+    return NDMG_OK;
+  }
   // z_1 .. z_m: pre-smoothing from z_0 = 0
   NDMG_TRY(smooth_level<T>(c, C, L, g, z, bt, 1, st));
   for (int l = 1; l < m; ++l) {
@@ -939,9 +978,9 @@ int vcycle_rec(ndmg_ctx* c, Cls& C, int k, const T* g, T* z, const ndmg::Bat& bt
   // gbar = I_k^{k-1} (g - A z_m)
   NDMG_HIP(ndmg::launch_apply<T>(z, g, P.r, L.g, bt, 1, st));
   NDMG_HIP(ndmg::launch_restrict<T>(P.r, at<T>(c, Lc.o_g), L.g, Lc.g, bt, st));
-  NDMG_TRY(vcycle_rec<T>(c, C, k - 1, at<T>(c, Lc.o_g), at<T>(c, Lc.o_z), bt, st));
+  NDMG_TRY(vcycle_rec<T>(c, C, k - 1, at<T>(c, Lc.o_g), zc, bt, st));
   // z_{m+1} = z_m + I_{k-1}^k MG(k-1, gbar, 0, m)
-  NDMG_HIP(ndmg::launch_prolong_add<T>(at<T>(c, Lc.o_z), z, L.g, Lc.g, bt, st));
+  NDMG_HIP(ndmg::launch_prolong_add<T>(zc, z, L.g, Lc.g, bt, st));
   // post-smoothing
   for (int l = 0; l < m; ++l) {
     NDMG_HIP(ndmg::launch_apply<T>(z, g, P.r, L.g, bt, 1, st));

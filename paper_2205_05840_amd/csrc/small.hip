@@ -1,0 +1,499 @@
+// Small levels of the V-cycle (vertex smoother, subdomains of 2 x 2 x 2 elements).
+//
+// On levels of up to 32^3 elements the separate kernels of a smoothing step (residual,
+// condensation, patch products, interface sum) and of the transfers take 4 to 7 us each, for
+// work of well under 1 us: each is a chain of two to four dependent memory round trips behind
+// a launch.  Here a launch does as much as one exchange between work items allows, and a
+// block or wavefront owns one item:
+//   k_small_patch     one block per vertex: everything the patch of a vertex V needs lies in
+//                     the 4^3 elements around V (108 inner edges, 300 edges in all).  The
+//                     block loads z and g there (and the coarse correction, which it
+//                     prolongs), forms the residual on the 108 inner edges, condenses it
+//                     onto the 60 slots, and multiplies by S_type^{-1}, one result row per
+//                     lane.  Each inner edge is computed by the up to 8 patches that hold it.
+//   k_small_pull      one wavefront per subdomain: sums the patch results on its 48 boundary
+//                     edges, extends them into its interior and updates its 24 unknowns.
+//   k_small_restrict  one block per coarse node: the 54 fine residuals its three edges
+//                     restrict, then the weighted sums.
+// All loads that do not depend on one another go out before the first wait, the convergence
+// flag's among them (tested before the first store).  What bounds them is latency: launch,
+// one or two round trips and the LDS phases.  Measured at 16^3 / 32^3 in FP32: 4.9 / 9.0 us
+// for prolongation, residual, condensation and patch products (separate kernels 19 / 20), 3.4
+// / 4.0 for the interface sum (7), 3.5 / 4.8 for residual and restriction (9).  A level takes
+// 5 launches instead of 10.  One wavefront per vertex instead of a block measured slower (6.9
+// us at 10^3: about 900 instructions one after another); so did the condensed residual as a
+// launch of its own before the MFMA patch products at every size.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "ndmg_internal.hpp"
+#include "small.hpp"
+
+namespace ndmg {
+
+namespace {
+
+__device__ __forceinline__ int64_t lin(const DGeom& g, int i, int j, int k) {
+  return (int64_t)k * g.plane + (int64_t)j * g.P + i;
+}
+
+// contiguous ranges of logical blocks per XCD (hardware deals blocks to the 8 XCDs in turn)
+__device__ __forceinline__ int xcd_block(int b, int nb) {
+  const int q = nb >> 3, r = nb & 7;
+  const int x = b & 7, i = b >> 3;
+  return x * q + min(x, r) + i;
+}
+
+// keeps the loads above it from sinking below a branch
+__device__ __forceinline__ void issue_barrier() { __asm__ volatile("" ::: "memory"); }
+
+// The cube of a vertex V: the nodes 2 V - 2 .. 2 V + 2 of each axis, an array [3][5][5][5]
+// of edges by their first node.  Wave d of a block works on the edges of direction d, so that
+// every stride is a constant.
+constexpr int kCube = 125;
+
+// Lower node of the cube of a vertex, and the position of a lane's entries in it.
+struct Cube {
+  int x0, y0, z0, n;
+  __device__ __forceinline__ bool inside(int x, int y, int z) const {
+    return (unsigned)(x0 + x) <= (unsigned)n && (unsigned)(y0 + y) <= (unsigned)n && (unsigned)(z0 + z) <= (unsigned)n;
+  }
+  // the edge of direction d at cube node (x, y, z) is an unknown
+  __device__ __forceinline__ bool unknown(int d, int x, int y, int z) const {
+    return x0 + x >= (d != 0) && y0 + y >= (d != 1) && z0 + z >= (d != 2) && x0 + x < n && y0 + y < n && z0 + z < n;
+  }
+};
+
+// entries lane and lane + 64 of direction d of v on the cube; 0 outside [0, n]^3
+template <typename T>
+__device__ __forceinline__ void load_cube(const T* __restrict__ v, const DGeom& g, const Cube& q, int d, int lane,
+                                          T (&out)[2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int m = min(lane + 64 * i, kCube - 1);
+    const int z = m / 25, m2 = m - z * 25, y = m2 / 5, x = m2 - y * 5;
+    const bool ok = q.inside(x, y, z);
+    const T t = v[ok ? d * g.B + lin(g, q.x0 + x, q.y0 + y, q.z0 + z) : 0];
+    out[i] = ok ? t : T(0);
+  }
+}
+
+// (A u)_e at the edge of direction D whose first node is position p of the cube in LDS: the
+// factorised form alpha h C^T M_F C + h^3 M_E, the 33 entries read once
+template <int D, typename T>
+__device__ __forceinline__ T apply_cube(const T* L, int p, T ah, T h3) {
+  constexpr int st[3] = {1, 5, 25};
+  constexpr int sa = st[D], sb = st[(D + 1) % 3], sc = st[(D + 2) % 3];
+  const T* ua = L + D * kCube + p;
+  const T* ub = L + (D + 1) % 3 * kCube + p;
+  const T* uc = L + (D + 2) % 3 * kCube + p;
+  const T t6 = T(1) / T(6), t23 = T(2) / T(3);
+  T A[3][3], Ub[2][3][2], Uc[2][3][2];   // offsets [b][c]; [b: -1, 0][c][a]; [c: -1, 0][b][a]
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) A[i][j] = ua[(i - 1) * sb + (j - 1) * sc];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        Ub[i][j][e] = ub[(i - 1) * sb + (j - 1) * sc + e * sa];
+        Uc[i][j][e] = uc[(i - 1) * sc + (j - 1) * sb + e * sa];
+      }
+  // faces of normal b at (c offset i - 1, b offset j - 1), and of normal c likewise
+  T Fb[2][3], Fc[2][3];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      Fb[i][j] = (A[j][i + 1] - A[j][i]) - (Uc[i][j][1] - Uc[i][j][0]);
+      Fc[i][j] = (Ub[i][j][1] - Ub[i][j][0]) - (A[i + 1][j] - A[i][j]);
+    }
+  T Gb[2], Gc[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    Gb[i] = t6 * (Fb[i][0] + Fb[i][2]) + t23 * Fb[i][1];
+    Gc[i] = t6 * (Fc[i][0] + Fc[i][2]) + t23 * Fc[i][1];
+  }
+  const T curl = (Gb[0] - Gb[1]) - (Gc[0] - Gc[1]);
+  T row[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) row[i] = t6 * (A[i][0] + A[i][2]) + t23 * A[i][1];
+  const T mass = t6 * (row[0] + row[2]) + t23 * row[1];
+  return ah * curl + h3 * mass;
+}
+
+// Position of an edge of direction d at offset a along it and b, c across (axes d + 1, d + 2).
+struct Pos {
+  int x, y, z;
+  __device__ __forceinline__ int lin() const { return x + 5 * y + 25 * z; }
+};
+__device__ __forceinline__ Pos edge_pos(int d, int a, int b, int c) {
+  return d == 0 ? Pos{a, b, c} : (d == 1 ? Pos{c, a, b} : Pos{b, c, a});
+}
+
+// I zc at the edge of direction D at cube node (x, y, z), from the coarse cube cL
+// ([3][3][3][3], coarse nodes V - 1 .. V + 1): weight 1/2 each side across an axis at an odd
+// offset (the cube's lower node is even)
+template <int D, typename T>
+__device__ __forceinline__ T prolong_cube(const T* cL, int x, int y, int z) {
+  const int o[3] = {x, y, z};
+  constexpr int st[3] = {1, 3, 9};
+  const int ob = o[(D + 1) % 3] & 1, oc = o[(D + 2) % 3] & 1;
+  const int sb = ob * st[(D + 1) % 3], sc = oc * st[(D + 2) % 3];
+  const T* e = cL + 27 * D + (x >> 1) + 3 * (y >> 1) + 9 * (z >> 1);
+  const T wb0 = ob ? T(0.5) : T(1), wb1 = ob ? T(0.5) : T(0);
+  const T wc0 = oc ? T(0.5) : T(1), wc1 = oc ? T(0.5) : T(0);
+  const T lo = wb0 * e[0] + wb1 * e[sb], hi = wb0 * e[sc] + wb1 * e[sb + sc];
+  return wc0 * lo + wc1 * hi;
+}
+
+// One block per vertex V.  MODE 0: r = g; 1: r = g - A z; 2: r = g - A (z + I zc).
+template <typename T, int MODE>
+__global__ void __launch_bounds__(256) k_small_patch(const T* __restrict__ g, const T* __restrict__ z,
+                                                     const T* __restrict__ zc, SmallSub<T> s, DGeom gc, Bat bt) {
+  constexpr int NG = 60, NPAD = 64, NX = 288, NC = NG / 4;
+  __shared__ T zL[MODE ? 3 * kCube : 1];
+  __shared__ T rL[3 * kCube];
+  __shared__ T cL[MODE == 2 ? 81 : 1];
+  __shared__ T xL[NX];
+  __shared__ __attribute__((aligned(16))) T gL[NPAD];
+  __shared__ T pL[4][NPAD];
+  const int nv = s.nH + 1, nv3 = nv * nv * nv;
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int pair = lb / nv3, v = lb - pair * nv3;
+  const int vx = v % nv, vy = (v / nv) % nv, vz = v / (nv * nv);
+  const int act = bt.act ? bt.act[pair] : 1;
+  const int prob = pair / bt.nrhs;
+  const T ah = MODE ? (T)(bt.alpha[prob] * s.h) : T(0);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t off = (int64_t)pair * 3 * s.g.B;
+  const Cube q{2 * vx - 2, 2 * vy - 2, 2 * vz - 2, s.g.n};
+  T zv[2], cv = T(0), gv = T(0), xv[5], sv[NC];
+  // this lane's inner edge of direction `wave`: offset 0 .. 3 along it, nodes 1 .. 3 across
+  const int il = min(lane, 35);
+  const Pos ip = edge_pos(wave, il & 3, 1 + (il >> 2) % 3, 1 + il / 12);
+  const bool iu = wave < 3 && q.unknown(wave, ip.x, ip.y, ip.z);
+  if (wave < 3) {
+    if constexpr (MODE != 0) load_cube(z + off, s.g, q, wave, lane, zv);
+    if constexpr (MODE == 2) {
+      const int m = min(lane, 26), w = m / 9, y = m / 3 % 3, x = m % 3;
+      const bool ok = (unsigned)(vx - 1 + x) <= (unsigned)gc.n && (unsigned)(vy - 1 + y) <= (unsigned)gc.n &&
+                      (unsigned)(vz - 1 + w) <= (unsigned)gc.n;
+      const T t = zc[(int64_t)pair * 3 * gc.B + (ok ? wave * gc.B + lin(gc, vx - 1 + x, vy - 1 + y, vz - 1 + w) : 0)];
+      cv = ok ? t : T(0);
+    }
+    gv = g[off + (iu ? wave * s.g.B + lin(s.g, q.x0 + ip.x, q.y0 + ip.y, q.z0 + ip.z) : 0)];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 5; ++i) xv[i] = s.XT[(int64_t)prob * NX + min(lane + 64 * i, NX - 1)];
+  }
+  // condensation: four lanes per slot, one subdomain each
+  const uint32_t* __restrict__ tab = s.tab + kSmallSlots + 5 * min(tid >> 2, NG - 1);
+  const uint32_t pos = tab[0], code = tab[1 + (tid & 3)];
+  const int type = (vx == 0 ? 0 : (vx == s.nH ? 2 : 1)) + 3 * (vy == 0 ? 0 : (vy == s.nH ? 2 : 1)) +
+                   9 * (vz == 0 ? 0 : (vz == s.nH ? 2 : 1));
+  // S^{-1} is symmetric: column k of this lane's row is entry (k, lane); wave w takes the
+  // columns 15 w .. 15 w + 14
+  const T* __restrict__ Sm = s.Sinv + prob * s.sstride + (int64_t)type * NPAD * NPAD + wave * NC * NPAD + lane;
+#pragma unroll
+  for (int k = 0; k < NC; ++k) sv[k] = Sm[k * NPAD];
+  issue_barrier();
+  if (act == 0) return;
+  if (wave == 3) {
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+      if (lane + 64 * i < NX) xL[lane + 64 * i] = xv[i];
+  } else if constexpr (MODE == 0) {
+    if (lane < 36) rL[wave * kCube + ip.lin()] = iu ? gv : T(0);
+  } else {
+    if constexpr (MODE == 2) {
+      if (lane < 27) cL[27 * wave + lane] = cv;
+    }
+    if constexpr (MODE == 1) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (lane + 64 * i < kCube) zL[wave * kCube + lane + 64 * i] = zv[i];
+    }
+  }
+  if constexpr (MODE == 2) {
+    // (a wave prolongs its own direction from the coarse entries it has just written)
+    auto prolong = [&](auto dir) {
+      constexpr int D = decltype(dir)::value;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int m = min(lane + 64 * i, kCube - 1);
+        const int w = m / 25, m2 = m - w * 25, y = m2 / 5, x = m2 - y * 5;
+        // (an entry past the last element along its direction is not an edge of the cube)
+        const T add = (D == 0 ? x : (D == 1 ? y : w)) < 4 ? prolong_cube<D>(cL, x, y, w) : T(0);
+        if (lane + 64 * i < kCube) zL[D * kCube + m] = zv[i] + add;
+      }
+    };
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (wave == 0) prolong(std::integral_constant<int, 0>{});
+    if (wave == 1) prolong(std::integral_constant<int, 1>{});
+    if (wave == 2) prolong(std::integral_constant<int, 2>{});
+  }
+  __syncthreads();
+  if constexpr (MODE != 0) {
+    const T h3 = (T)(s.h * s.h * s.h);
+    const int p = ip.lin();
+    T ax = T(0);
+    if (wave == 0) ax = apply_cube<0>(zL, p, ah, h3);
+    if (wave == 1) ax = apply_cube<1>(zL, p, ah, h3);
+    if (wave == 2) ax = apply_cube<2>(zL, p, ah, h3);
+    if (wave < 3 && lane < 36) rL[wave * kCube + p] = iu ? gv - ax : T(0);
+    __syncthreads();
+  }
+  T c = T(0);
+  {
+    // interior unknown t of subdomain sd of the cube: a constant offset from its lower node
+    constexpr int io[6] = {30, 31, kCube + 26, kCube + 31, 2 * kCube + 6, 2 * kCube + 31};
+    const bool on = code != 0xffff;
+    const int sd = code & 7, e = on ? (int)(code >> 3) : 0;
+    const T* rq = rL + 2 * (sd & 1) + 10 * ((sd >> 1) & 1) + 50 * (sd >> 2);
+#pragma unroll
+    for (int t = 0; t < 6; ++t) c += xL[t * 48 + e] * rq[io[t]];
+    c = on ? c : T(0);
+  }
+  c += __shfl_xor(c, 1, 64);
+  c += __shfl_xor(c, 2, 64);
+  if constexpr (MODE != 0) {
+    // r on the interior of the subdomain whose lower corner is V
+    if (wave == 1 && lane < 6 && vx < s.nH && vy < s.nH && vz < s.nH) {
+      const int d = lane >> 1, f = lane & 1;   // (order of interior_dofs)
+      const int ex = d == 0 ? f : 1, ey = d == 1 ? f : 1, ez = d == 2 ? f : 1;
+      s.r[off + d * s.g.B + lin(s.g, 2 * vx + ex, 2 * vy + ey, 2 * vz + ez)] =
+          rL[d * kCube + (2 + ex) + 5 * (2 + ey) + 25 * (2 + ez)];
+    }
+  }
+  if ((tid & 3) == 0) gL[tid >> 2] = tid < 4 * NG ? rL[pos] - c : T(0);
+  __syncthreads();
+  T y = T(0);
+#pragma unroll
+  for (int k = 0; k < NC; ++k) y += sv[k] * gL[wave * NC + k];
+  pL[wave][lane] = y;
+  __syncthreads();
+  if (wave == 0) s.Y[((int64_t)pair * nv3 + v) * NPAD + lane] = (pL[0][lane] + pL[1][lane]) + (pL[2][lane] + pL[3][lane]);
+}
+
+// Lane e < 48: boundary edge e of the subdomain; lanes 48 .. 53: its interior unknowns.
+// Bound by latency: one round trip for the table, one for everything else.
+template <typename T>
+__global__ void __launch_bounds__(64) k_small_pull(const T* __restrict__ r, T* z, const T* __restrict__ zc,
+                                                   int assign, SmallSub<T> s, DGeom gc, Bat bt) {
+  constexpr int NPAD = 64, NX = 288;
+  __shared__ T wL[48];
+  const int nH = s.nH, nv = nH + 1, nv3 = nv * nv * nv, ns = nH * nH * nH;
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int pair = lb / ns, u = lb - pair * ns;
+  const int a = u % nH, b = (u / nH) % nH, c = u / (nH * nH);
+  const int act = bt.act ? bt.act[pair] : 1;
+  const int prob = pair / bt.nrhs;
+  const int lane = threadIdx.x;
+  const int64_t off = (int64_t)pair * 3 * s.g.B;
+  const uint32_t* __restrict__ tab = s.tab + kSmallEdges + 5 * min(lane, 53);
+  const uint32_t tx = tab[0], c0 = tab[1], c1 = tab[2], c2 = tab[3], c3 = tab[4];
+  // interior rows: lane 8 t + p takes columns 6 p .. 6 p + 5 of row t of X_T, and column p
+  // of A_T^{-1}
+  const int t = min(lane >> 3, 5), p = lane & 7;
+  T xr[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) xr[i] = s.XT[(int64_t)prob * NX + t * 48 + 6 * p + i];
+  const T ai = s.ATinv[(int64_t)prob * 36 + 6 * t + min(p, 5)];
+  T ri;
+  {
+    const int q = min(p, 5), d = q >> 1, f = q & 1;
+    ri = r[off + d * s.g.B + lin(s.g, 2 * a + (d == 0 ? f : 1), 2 * b + (d == 1 ? f : 1), 2 * c + (d == 2 ? f : 1))];
+  }
+  const int d = tx & 3, ox = (tx >> 2) & 3, oy = (tx >> 4) & 3, oz = (tx >> 6) & 3;
+  const bool mine = (tx >> 8) & 1;
+  const int64_t at = off + d * s.g.B + lin(s.g, 2 * a + ox, 2 * b + oy, 2 * c + oz);
+  const T zo = assign ? T(0) : z[at];
+  T pe[4] = {T(0), T(0), T(0), T(0)};
+  const int ob = (d == 0 ? oy : (d == 1 ? oz : ox)) & 1, oc = (d == 0 ? oz : (d == 1 ? ox : oy)) & 1;
+  if (zc) {
+    const int64_t st[3] = {1, (int64_t)gc.P, gc.plane};
+    const int64_t sb = ob ? (d == 0 ? st[1] : (d == 1 ? st[2] : st[0])) : 0;
+    const int64_t sc = oc ? (d == 0 ? st[2] : (d == 1 ? st[0] : st[1])) : 0;
+    const T* e = zc + (int64_t)pair * 3 * gc.B + d * gc.B + lin(gc, a + (ox >> 1), b + (oy >> 1), c + (oz >> 1));
+    pe[0] = e[0];
+    pe[1] = e[sb];
+    pe[2] = e[sc];
+    pe[3] = e[sb + sc];
+  }
+  const T* __restrict__ Yp = s.Y + (int64_t)pair * nv3 * NPAD;
+  auto patch = [&](unsigned code) {
+    const bool on = code != 0xffff;
+    const int q = code & 7, slot = on ? (int)(code >> 3) : 0;
+    const int x = a + (q & 1), y = b + ((q >> 1) & 1), w = c + (q >> 2);
+    const T val = Yp[((w * nv + y) * nv + x) * NPAD + slot];
+    return on ? val : T(0);
+  };
+  const T y0 = patch(c0), y1 = patch(c1), y2 = patch(c2), y3 = patch(c3);
+  issue_barrier();
+  if (act == 0) return;
+  const T w = ((y0 + y1) + y2) + y3;
+  if (lane < 48) wL[lane] = w;
+  __syncthreads();
+  T sum = p < 6 ? ai * ri : T(0);
+#pragma unroll
+  for (int i = 0; i < 6; ++i) sum -= xr[i] * wL[6 * p + i];
+#pragma unroll
+  for (int m = 1; m < 8; m <<= 1) sum += __shfl_xor(sum, m, 64);
+  const T zi = __shfl(sum, 8 * max(min(lane - 48, 5), 0), 64);
+  const T wb0 = ob ? T(0.5) : T(1), wb1 = ob ? T(0.5) : T(0), wc0 = oc ? T(0.5) : T(1), wc1 = oc ? T(0.5) : T(0);
+  const T pro = wc0 * (wb0 * pe[0] + wb1 * pe[1]) + wc1 * (wb0 * pe[2] + wb1 * pe[3]);
+  if (mine && lane < 54) z[at] = (zo + pro) + (T)s.eta * (lane < 48 ? w : zi);
+}
+
+// Lane of wave d: offset 0 / 1 along the direction d, -1 .. 1 across, of the 18 fine edges
+// that the coarse edge of direction d at node V restricts.
+template <typename T>
+__global__ void __launch_bounds__(192) k_small_restrict(const T* __restrict__ g, const T* __restrict__ z,
+                                                        T* __restrict__ out, DGeom f, double h, DGeom c, Bat bt) {
+  __shared__ T zL[3 * kCube];
+  __shared__ T rL[54];
+  const int nc = c.n, nc3 = nc * nc * nc;
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int pair = lb / nc3, v = lb - pair * nc3;
+  const int vx = v % nc, vy = (v / nc) % nc, vz = v / (nc * nc);
+  const int act = bt.act ? bt.act[pair] : 1;
+  const T ah = (T)(bt.alpha[pair / bt.nrhs] * h), h3 = (T)(h * h * h);
+  const int lane = threadIdx.x & 63, d = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t off = (int64_t)pair * 3 * f.B;
+  const Cube q{2 * vx - 2, 2 * vy - 2, 2 * vz - 2, f.n};
+  T zv[2];
+  load_cube(z + off, f, q, d, lane, zv);
+  const int l = min(lane, 17);
+  const Pos e = edge_pos(d, 2 + (l & 1), 1 + (l >> 1) % 3, 1 + l / 6);
+  const bool on = q.unknown(d, e.x, e.y, e.z);
+  const T gv = g[off + (on ? d * f.B + lin(f, q.x0 + e.x, q.y0 + e.y, q.z0 + e.z) : 0)];
+  issue_barrier();
+  if (act == 0) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (lane + 64 * i < kCube) zL[d * kCube + lane + 64 * i] = zv[i];
+  __syncthreads();
+  T ax = T(0);
+  if (d == 0) ax = apply_cube<0>(zL, e.lin(), ah, h3);
+  if (d == 1) ax = apply_cube<1>(zL, e.lin(), ah, h3);
+  if (d == 2) ax = apply_cube<2>(zL, e.lin(), ah, h3);
+  if (lane < 18) rL[18 * d + lane] = on ? gv - ax : T(0);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (lane == 0) {
+    const T* s = rL + 18 * d;
+    T acc = T(0);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {   // the two fine edges along the coarse one
+      const T mid = T(0.5) * (s[k + 2] + s[k + 14]) + s[k + 8];
+      const T lo = T(0.5) * (s[k] + s[k + 12]) + s[k + 6];
+      const T hi = T(0.5) * (s[k + 4] + s[k + 16]) + s[k + 10];
+      acc += T(0.5) * (lo + hi) + mid;
+    }
+    out[(int64_t)pair * 3 * c.B + d * c.B + lin(c, vx, vy, vz)] =
+        vx >= (d != 0) && vy >= (d != 1) && vz >= (d != 2) ? acc : T(0);
+  }
+}
+
+}  // namespace
+
+namespace {
+
+std::vector<uint32_t> make_tables() {
+  std::vector<uint32_t> t(kSmallWords, 0);
+  auto set = [&](int at, uint32_t x, const std::vector<uint32_t>& codes) {
+    t[at] = x;
+    for (size_t i = 0; i < 4; ++i) t[at + 1 + i] = i < codes.size() ? codes[i] : 0xffff;
+  };
+  const std::vector<Slot> bd = boundary_dofs(2), in = interior_dofs(2), sl = vertex_slots(2);
+  const std::vector<int> bp = boundary_patch_table();
+  auto word = [](const Slot& q, bool own) {
+    return (uint32_t)(q.d | q.dx << 2 | q.dy << 4 | q.dz << 6 | (own ? 1 : 0) << 8);
+  };
+  for (size_t e = 0; e < bd.size(); ++e) {
+    std::vector<uint32_t> codes;
+    for (int k = 0; k < 4; ++k) {
+      const int code = bp[4 * e + k];
+      if (code >= 0) codes.push_back((uint32_t)(code & ~(1 << 30)));
+    }
+    set(kSmallEdges + 5 * (int)e, word(bd[e], bd[e].dx <= 1 && bd[e].dy <= 1 && bd[e].dz <= 1), codes);
+  }
+  for (size_t i = 0; i < in.size(); ++i) set(kSmallEdges + 5 * (48 + (int)i), word(in[i], true), {});
+  for (size_t i = 0; i < sl.size(); ++i) {
+    const int o[3] = {2 + sl[i].dx, 2 + sl[i].dy, 2 + sl[i].dz};
+    std::vector<uint32_t> codes;
+    for (int q = 0; q < 8; ++q)
+      for (size_t e = 0; e < bd.size(); ++e)
+        if (bd[e].d == sl[i].d && 2 * (q & 1) + bd[e].dx == o[0] && 2 * ((q >> 1) & 1) + bd[e].dy == o[1] &&
+            2 * (q >> 2) + bd[e].dz == o[2])
+          codes.push_back((uint32_t)(q | (int)e << 3));
+    set(kSmallSlots + 5 * (int)i, (uint32_t)(sl[i].d * kCube + o[0] + 5 * o[1] + 25 * o[2]), codes);
+  }
+  return t;
+}
+
+}  // namespace
+
+const std::vector<uint32_t>& small_tables() {
+  static const std::vector<uint32_t> t = make_tables();
+  return t;
+}
+
+// Measured on MI355X (us per CG iteration of one problem, large-level kernels / these, the
+// levels below on these): 16^3 FP32 79 / 55, FP64 85 / 56; 24^3 97 / 79, 104 / 85; 32^3 105 /
+// 100, 119 / 115; 40^3 135 / 149, 157 / 183; 48^3 146 / 191.  The work grows with the
+// vertices of all pairs, each reading its own S^{-1} and repeating its neighbours' residuals,
+// while the large-level kernels' time below 32^3 is their round trips; the two cross between
+// 17^3 and 21^3 vertices.
+bool small_level(int nH, int count) {
+  const int64_t nv = nH + 1;
+  return nv * nv * nv * count <= 6000;
+}
+
+template <typename T>
+hipError_t launch_small_patch(int mode, const T* g, const T* z, const T* zc, const SmallSub<T>& s, const DGeom& gc,
+                              const Bat& bt, hipStream_t st) {
+  const dim3 grid((unsigned)((s.nH + 1) * (s.nH + 1) * (s.nH + 1) * bt.count));
+  if (mode == 0)
+    hipLaunchKernelGGL((k_small_patch<T, 0>), grid, dim3(256), 0, st, g, z, zc, s, gc, bt);
+  else if (mode == 1)
+    hipLaunchKernelGGL((k_small_patch<T, 1>), grid, dim3(256), 0, st, g, z, zc, s, gc, bt);
+  else
+    hipLaunchKernelGGL((k_small_patch<T, 2>), grid, dim3(256), 0, st, g, z, zc, s, gc, bt);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_small_pull(const T* r, T* z, const T* zc, int assign, const SmallSub<T>& s, const DGeom& gc,
+                             const Bat& bt, hipStream_t st) {
+  hipLaunchKernelGGL((k_small_pull<T>), dim3((unsigned)(s.nH * s.nH * s.nH * bt.count)), dim3(64), 0, st, r, z, zc,
+                     assign, s, gc, bt);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_small_restrict(const T* g, const T* z, T* out, const DGeom& f, double h, const DGeom& c,
+                                 const Bat& bt, hipStream_t st) {
+  hipLaunchKernelGGL((k_small_restrict<T>), dim3((unsigned)(c.n * c.n * c.n * bt.count)), dim3(192), 0, st, g, z, out,
+                     f, h, c, bt);
+  return hipGetLastError();
+}
+
+#define NDMG_SMALL(T)                                                                                            \
+  template hipError_t launch_small_patch<T>(int, const T*, const T*, const T*, const SmallSub<T>&, const DGeom&, \
+                                            const Bat&, hipStream_t);                                            \
+  template hipError_t launch_small_pull<T>(const T*, T*, const T*, int, const SmallSub<T>&, const DGeom&,        \
+                                           const Bat&, hipStream_t);                                             \
+  template hipError_t launch_small_restrict<T>(const T*, const T*, T*, const DGeom&, double, const DGeom&,       \
+                                               const Bat&, hipStream_t);
+NDMG_SMALL(double)
+NDMG_SMALL(float)
+
+}  // namespace ndmg
