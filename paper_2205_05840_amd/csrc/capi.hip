@@ -80,6 +80,11 @@ struct LevelHost {
   // generic smoother (edge spaces, or subdomains of size 4): tables and factors
   bool gen = false;
   ndmg::GenTables gt;
+  // coefficient boxes on the vertex smoother (subdomains of 2): patch classes, factors per box
+  ndmg::BoxPatches bx;
+  size_t o_cls = 0;
+  int64_t yrow = 0;                    // row length of Y
+  int ntypes = 27;                     // patch matrices per problem
   size_t o_C = 0, o_gX = 0, o_gE = 0, o_gS = 0, blk_gX = 0, blk_gE = 0, blk_gS = 0;
   size_t o_guI = 0, o_grI = 0, o_grE = 0, o_gcI = 0, o_guP = 0, o_grP = 0, o_gcP = 0, o_ggam = 0, o_gcc = 0,
          o_gcodes = 0;
@@ -243,11 +248,10 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
       if (sizes[k] % s) return fail(NDMG_EINVAL, "level not divisible by the subdomain size");
       L.smoothed = true;
       L.sub = ndmg::make_sub(s, sizes[k]);
-      if (pl.opts.smoother == NDMG_SMOOTHER_EDGE || s != 2 || cf.r > 0) {
-        // the generic smoother: gathered products over subdomains and patches (also every
-        // level of a coefficient with jumps: its factors differ from box to box)
+      std::string err;
+      if (pl.opts.smoother == NDMG_SMOOTHER_EDGE || s != 2) {
+        // the generic smoother: gathered products over subdomains and patches
         L.gen = true;
-        std::string err;
         if (!ndmg::build_gen_tables(L.g, s, pl.opts.smoother == NDMG_SMOOTHER_EDGE ? 1 : 0,
                                     pl.opts.boundary_patches != 0, &L.gt, &err, cf))
           return fail(NDMG_EINVAL, err);
@@ -283,13 +287,25 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
         C.lv.push_back(std::move(L));
         continue;
       }
-      L.segs = ndmg::vertex_segments(L.sub.nH, pl.opts.boundary_patches != 0);
+      if (cf.r > 0) {
+        if (!ndmg::build_box_patches(L.g, pl.opts.boundary_patches != 0, cf, &L.bx, &err))
+          return fail(NDMG_EINVAL, err);
+        L.segs = L.bx.segs;
+        L.yrow = L.bx.yrow;
+        L.ntypes = (int)L.bx.geom.size();
+      } else {
+        L.segs = ndmg::vertex_segments(L.sub.nH, pl.opts.boundary_patches != 0);
+        L.yrow = ndmg::y_row_len(L.sub.nH);
+      }
+      // the interior segment, whose slots are all present; with boxes every segment counts
+      // as one (most lie inside the cube)
+      auto inner = [&](const ndmg::Segment& sg) { return cf.r > 0 || sg.type == 13; };
       L.chunks.clear();
       int64_t groups = 0;
       for (const auto& sg : L.segs) groups += (sg.count + 15) / 16;
       L.gpw = ndmg::patch_groups(groups * C.count, el);
       int tuned_i = 0, tuned_b = 0;
-      const bool tuned = ndmg::tune_lookup(ndmg::kTunePatch, sizes[k], (int)el, 0, C.count, &tuned_i, &tuned_b) &&
+      const bool tuned = cf.r == 0 && ndmg::tune_lookup(ndmg::kTunePatch, sizes[k], (int)el, 0, C.count, &tuned_i, &tuned_b) &&
                          tuned_i >= 1 && tuned_i <= 8 && tuned_b >= 1 && tuned_b <= 8;
       if (tuned) L.gpw = tuned_i;
       // Boundary-type segments check every slot against the domain, so their groups cost
@@ -297,7 +313,7 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
       // resident at once (else as many as the interior), so that they do not finish last.
       auto nchunks_with = [&](int gb) {
         int64_t nch = 0;
-        for (const auto& sg : L.segs) nch += (sg.count + 64 * (sg.type == 13 ? L.gpw : gb) - 1) / (64 * (sg.type == 13 ? L.gpw : gb));
+        for (const auto& sg : L.segs) nch += (sg.count + 64 * (inner(sg) ? L.gpw : gb) - 1) / (64 * (inner(sg) ? L.gpw : gb));
         return nch * C.count;
       };
       int gpw_b = L.gpw;
@@ -307,7 +323,7 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
       for (size_t si = 0; si < L.segs.size(); ++si) {
         // and no more per wave than spreads a small segment over the 4 waves of one chunk
         const int gseg = (L.segs[si].count + 15) / 16;
-        const int gs = std::max(1, std::min(L.segs[si].type == 13 ? L.gpw : gpw_b, (gseg + 3) / 4));
+        const int gs = std::max(1, std::min(inner(L.segs[si]) ? L.gpw : gpw_b, (gseg + 3) / 4));
         // A segment of one group (a short edge of the box) in a class of several
         // right-hand sides: one workgroup per 4 right-hand sides of a problem, one per
         // wave (they share S^{-1}), instead of a workgroup per pair with 3 idle waves.
@@ -330,7 +346,7 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
       // vertex range with the groups dealt out in turn, wave after wave, so that at any
       // time the XCD's waves work on one band of vertices whose gathered entries fit its
       // L2, instead of each wave on its own stretch across the XCD's whole range.
-      if (C.count == 1) {
+      if (C.count == 1 && cf.r == 0) {
         const int nch = (int)(L.chunks.size() / 4);
         int c0 = -1, c1 = -1;
         for (int j = 0; j < nch; ++j)
@@ -357,15 +373,17 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
       L.o_w = take(vb);
       const size_t nv = (size_t)(L.sub.nH + 1);
       // row positions in bytes fit in 32 bits (the smoother's reads of Y assume it)
-      if (ndmg::y_row_len(L.sub.nH) * 8 > UINT32_MAX) return fail(NDMG_EINVAL, "level too large for the patch result rows");
-      L.nY = std::max<size_t>(nv * nv * nv, (size_t)ndmg::y_row_len(L.sub.nH)) * (size_t)L.sub.npad;
+      if (L.yrow * 8 > UINT32_MAX) return fail(NDMG_EINVAL, "level too large for the patch result rows");
+      L.nY = std::max<size_t>(nv * nv * nv, (size_t)L.yrow) * (size_t)L.sub.npad;
       L.o_Y = take(L.nY * el * cnt);
       // gathered patch inputs of the one-launch bottom of the V-cycle (small levels)
       if (sizes[k] <= pl.opts.bottom_n) L.o_G = take(L.nY * el * cnt);
       L.nB = (int)ndmg::boundary_dofs(L.sub.s).size();
-      L.blk_ATinv = (size_t)L.sub.nI * L.sub.nI;
-      L.blk_XT = (size_t)L.sub.nI * L.nB;
-      L.blk_Sinv = (size_t)27 * L.sub.npad * L.sub.npad;
+      const size_t nbox = cf.r > 0 ? pl.coef.size() : 1;
+      L.blk_ATinv = nbox * L.sub.nI * L.sub.nI;
+      L.blk_XT = nbox * L.sub.nI * L.nB;
+      L.blk_Sinv = (size_t)L.ntypes * L.sub.npad * L.sub.npad;
+      if (cf.r > 0) L.o_cls = take(L.bx.cls.size() * sizeof(int));
       L.o_ATinv = take(L.blk_ATinv * el * np);
       L.o_XT = take(L.blk_XT * el * np);
       L.o_Sinv = take(L.blk_Sinv * el * np);
@@ -520,6 +538,11 @@ ndmg::DSub level_dsub(ndmg_ctx* c, const LevelHost& L) {
   d.chunks = at<int>(c, L.o_chunks);
   d.nchunks = (int)(L.chunks.size() / 4);
   d.bofs = at<int64_t>(c, L.o_bofs);
+  d.yrow = L.yrow;
+  d.ntypes = L.ntypes;
+  d.r = L.bx.r;
+  d.w = L.bx.w;
+  d.cls = d.r > 0 ? at<int>(c, L.o_cls) : nullptr;
   return d;
 }
 
@@ -529,13 +552,15 @@ ndmg::SmallSub<T> small_sub(ndmg_ctx* c, const Cls& C, const LevelHost& L) {
                            L.g.h,
                            L.sub.nH,
                            at<uint32_t>(c, C.o_tab),
+                           L.bx.r > 0 ? at<int>(c, L.o_cls) : nullptr,
                            at<T>(c, L.o_ATinv),
                            at<T>(c, L.o_XT),
                            at<T>(c, L.o_Sinv),
                            (int64_t)L.blk_Sinv,
                            at<T>(c, L.o_Y),
                            at<T>(c, L.o_r),
-                           c->plan.opts.eta};
+                           c->plan.opts.eta,
+                           L.bx.r > 0 ? ndmg::BoxDiv(L.bx.w) : ndmg::BoxDiv()};
 }
 
 // All pairs of a class, or only its active ones.
@@ -649,6 +674,41 @@ bool build_gen_factors(const LevelHost& L, double alpha, T* xc, T* ex, T* sp, st
       }
     T* dst = sp + (size_t)type * tb.npadP * tb.npadP;
     for (size_t i = 0; i < buf.size(); ++i) dst[i] = (T)buf[i];
+  }
+  return true;
+}
+
+// FP64 factors of a level of the vertex smoother with coefficient boxes, cast to T: per box
+// A_T^{-1} and X_T (zero outside the domain), per patch type S^{-1} (type 0: zero).
+template <typename T>
+bool build_box_factors(const LevelHost& L, double alpha, const ndmg::CoefBoxes& cf, T* ai, T* xt, T* sp,
+                       std::string* err) {
+  const int nI = L.sub.nI, nB = L.nB, npad = L.sub.npad;
+  std::vector<double> a, x;
+  for (int b = 0; b < cf.r * cf.r * cf.r; ++b) {
+    if (!(cf.v[b] > 0.0)) continue;
+    if (!ndmg::subdomain_factors(2, L.g.h, alpha * cf.v[b], &a, &x, err)) return false;
+    for (int i = 0; i < nI * nI; ++i) ai[(size_t)b * nI * nI + i] = (T)a[i];
+    for (int i = 0; i < nI * nB; ++i) xt[(size_t)b * nI * nB + i] = (T)x[i];
+  }
+  const std::vector<ndmg::Slot> slots = ndmg::vertex_slots(2);
+  std::vector<double> buf((size_t)npad * npad), cell_alpha;
+  std::vector<char> present;
+  for (int type = 1; type < L.ntypes; ++type) {
+    int t[3];
+    ndmg::patch_type_axes(0, L.bx.geom[type], t);
+    std::vector<std::array<int, 3>> kept;
+    cell_alpha.clear();
+    for (const auto& q : ndmg::patch_cells(0, L.bx.geom[type], 2)) {
+      const double f = L.bx.key[type][(q[0] >= 0 ? 1 : 0) | (q[1] >= 0 ? 2 : 0) | (q[2] >= 0 ? 4 : 0)];
+      if (!(f > 0.0)) continue;
+      kept.push_back(q);
+      cell_alpha.push_back(alpha * f);
+    }
+    if (!ndmg::patch_inverse(kept, slots, t, 2, L.g.h, alpha, npad, buf.data(), &present, err, &cell_alpha,
+                             &L.bx.present[type]))
+      return false;
+    for (size_t i = 0; i < buf.size(); ++i) sp[(size_t)type * npad * npad + i] = (T)buf[i];
   }
   return true;
 }
@@ -792,6 +852,13 @@ int build_class_factors(ndmg_ctx* c, Cls& C, Staging& stg) {
           }
           continue;
         }
+        if (L.bx.r > 0) {
+          if (!build_box_factors(L, a, pl.boxes(), ATinv[k].data(), XT[k].data(), Sinv[k].data(), &err)) {
+            errs[t] = err;
+            return;
+          }
+          continue;
+        }
         if (!ndmg::build_level_factors_into<T>(L.g.h, a, L.sub, bp, ATinv[k].data() + (size_t)p * L.blk_ATinv,
                                                XT[k].data() + (size_t)p * L.blk_XT,
                                                Sinv[k].data() + (size_t)p * L.blk_Sinv, &err)) {
@@ -860,20 +927,22 @@ int build_class_factors(ndmg_ctx* c, Cls& C, Staging& stg) {
     }
     NDMG_TRY(stg.put_vec(c, L.o_slots, sl));
     std::vector<int> sg;
-    for (auto& q : L.segs) {
+    for (size_t i = 0; i < L.segs.size(); ++i) {
+      const ndmg::Segment& q = L.segs[i];
       sg.push_back(q.type);
       for (int a = 0; a < 3; ++a) sg.push_back(q.lo[a]);
       for (int a = 0; a < 2; ++a) sg.push_back(q.dims[a]);
-      const int nH = L.sub.nH;
-      const int yb = ndmg::y_pos(nH, c->plan.opts.boundary_patches != 0, q.lo[0], q.lo[1], q.lo[2]);
+      const int yb = L.bx.r > 0 ? L.bx.segY[i]
+                                : ndmg::y_pos(L.sub.nH, c->plan.opts.boundary_patches != 0, q.lo[0], q.lo[1], q.lo[2]);
       if (yb % 16) return fail(NDMG_EINVAL, "internal: patch result region not on a 16-entry run");
-      sg.push_back((int)yb);
+      sg.push_back(yb);
       sg.push_back(q.count);
     }
+    if (L.bx.r > 0) NDMG_TRY(stg.put_vec(c, L.o_cls, L.bx.cls));
     NDMG_TRY(stg.put_vec(c, L.o_segs, sg));
     NDMG_TRY(stg.put_vec(c, L.o_chunks, L.chunks));
     if (k == C.dense_k) {
-      L.map = ndmg::unknown_offsets(L.g);
+      L.map = ndmg::unknown_offsets(L.g, pl.boxes());
       if ((int)L.map.size() != L.Nd) return fail(NDMG_EINVAL, "internal: dense level size mismatch");
       NDMG_TRY(stg.put_vec(c, L.o_map, L.map));
     }

@@ -769,6 +769,86 @@ bool patch_inverse(const std::vector<std::array<int, 3>>& cells, const std::vect
   return true;
 }
 
+bool build_box_patches(const Geom& g, bool boundary, const CoefBoxes& cf, BoxPatches* out, std::string* err) {
+  const int n = g.n, nH = n / 2, r = cf.r;
+  if (n % r || (n / r) % 2) {
+    *err = "every subdomain must lie in one box of the coefficient: n_k / r must be a multiple of the "
+           "subdomain size on every smoothed level";
+    return false;
+  }
+  BoxPatches& b = *out;
+  b = BoxPatches{};
+  b.r = r;
+  b.w = nH / r;
+  const int K = 2 * r + 1;
+  b.cls.assign((size_t)2 * K * K * K, 0);
+  const std::vector<Slot> slots = vertex_slots(2);
+  b.geom.push_back(-1);   // type 0: no patch
+  b.key.push_back({});
+  b.present.emplace_back();
+  std::map<std::pair<int, std::array<double, 8>>, int> index;
+  std::vector<int> none;   // class triples without a patch
+  for (int cz = 0; cz < K; ++cz)
+    for (int cy = 0; cy < K; ++cy)
+      for (int cx = 0; cx < K; ++cx) {
+        const int c[3] = {cx, cy, cz}, at = (cz * K + cy) * K + cx;
+        Segment sg;
+        sg.count = 1;
+        int t[3], nb = 0;
+        for (int ax = 0; ax < 3; ++ax) {
+          sg.lo[ax] = c[ax] / 2 * b.w + (c[ax] & 1);
+          sg.dims[ax] = (c[ax] & 1) ? b.w - 1 : 1;
+          sg.count *= sg.dims[ax];
+          t[ax] = c[ax] == 0 ? 0 : (c[ax] == K - 1 ? 2 : 1);
+          nb += t[ax] != 1;
+        }
+        const int geom = t[0] + 3 * t[1] + 9 * t[2];
+        int type = 0;
+        // (box corners have no interface unknowns)
+        if (sg.count > 0 && nb < 3 && (boundary || nb == 0)) {
+          const int o[3] = {2 * sg.lo[0], 2 * sg.lo[1], 2 * sg.lo[2]};
+          std::array<double, 8> key;
+          for (int q = 0; q < 8; ++q)
+            key[q] = cf.at(n, o[0] + (q & 1) - 1, o[1] + ((q >> 1) & 1) - 1, o[2] + ((q >> 2) & 1) - 1);
+          const auto k = std::make_pair(geom, key);
+          auto it = index.find(k);
+          if (it == index.end()) {
+            std::vector<char> pres = patch_slots_present(patch_cells(0, geom, 2), slots, t);
+            bool any = false;
+            for (size_t j = 0; j < slots.size(); ++j) {
+              const Slot& q = slots[j];
+              pres[j] = pres[j] && cf.edge_in(n, q.d, o[0] + q.dx, o[1] + q.dy, o[2] + q.dz);
+              any = any || pres[j];
+            }
+            it = index.emplace(k, any ? (int)b.geom.size() : 0).first;
+            if (any) {
+              b.geom.push_back(geom);
+              b.key.push_back(key);
+              b.present.push_back(pres);
+            }
+          }
+          type = it->second;
+        }
+        b.cls[2 * at + 1] = type;
+        if (type == 0) {
+          none.push_back(at);
+          continue;
+        }
+        sg.type = type;
+        b.cls[2 * at] = (int)b.yrow;
+        b.segs.push_back(sg);
+        b.segY.push_back((int)b.yrow);
+        b.yrow += (sg.count + 15) / 16 * 16;
+      }
+  for (int at : none) b.cls[2 * at] = (int)b.yrow;
+  b.yrow += 16;
+  if (b.segs.size() > 0xffff) {
+    *err = "too many patch segments";
+    return false;
+  }
+  return true;
+}
+
 bool build_gen_tables(const Geom& g, int s, int kind, bool boundary, GenTables* out, std::string* err,
                       const CoefBoxes& cf) {
   const int n = g.n, nH = n / s;

@@ -91,6 +91,23 @@ __device__ __forceinline__ bool box_position(const int3& bk, int w, int nbx, int
 }
 
 
+// Subdomain (a, b, c) of this thread on a level with coefficient boxes: block `bi` of the
+// pair takes blockDim.x consecutive subdomains of one box (r^3 boxes of w^3 subdomains);
+// o = position in the box; valid false past its end.  Returns the box.
+__device__ __forceinline__ int box_subdomain(int bi, int r, int w, int& a, int& b, int& c, int (&o)[3], bool& valid) {
+  const int w3 = w * w * w, nbb = (w3 + (int)blockDim.x - 1) / (int)blockDim.x;
+  const int box = bi / nbb, t = (bi - box * nbb) * (int)blockDim.x + (int)threadIdx.x;
+  valid = t < w3;
+  const int u = valid ? t : 0;
+  o[0] = u % w;
+  o[1] = (u / w) % w;
+  o[2] = u / (w * w);
+  a = box % r * w + o[0];
+  b = box / r % r * w + o[1];
+  c = box / (r * r) * w + o[2];
+  return box;
+}
+
 template <typename T>
 __device__ __forceinline__ T apply_at(const T* __restrict__ u, const DGeom& g, int a, int64_t p,
                                       T ah, T h3) {
@@ -541,7 +558,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (BUF ? 5 : 1) : 3)
   const bool wact = __builtin_amdgcn_readfirstlane(
       !rhsw || ((pair % bt.nrhs) + wave < bt.nrhs && !inactive(bt, pair + wave)));
   const int wpair = __builtin_amdgcn_readfirstlane(rhsw && wact ? pair + wave : pair);
-  const int64_t NVY = y_row_len(sub.nH);
+  const int64_t NVY = sub.yrow;
   gg += (int64_t)wpair * vlen(g);
   Y += (int64_t)wpair * NVY * NPAD;
   const int seg = cw & 0xffff;
@@ -560,7 +577,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (BUF ? 5 : 1) : 3)
   const int d1 = __builtin_amdgcn_readfirstlane(sg[5]);
   const int ybase = __builtin_amdgcn_readfirstlane(sg[6]);
   const int count = __builtin_amdgcn_readfirstlane(sg[7]);
-  const T* __restrict__ Sm = Sinv + ((int64_t)(pair / bt.nrhs) * 27 + type) * NPAD * NPAD;
+  const T* __restrict__ Sm = Sinv + ((int64_t)(pair / bt.nrhs) * sub.ntypes + type) * NPAD * NPAD;
   for (int e = tid; e < NPAD; e += blockDim.x) {
     int rel = 0, pres = 0;
     if (e < NG) {
@@ -758,7 +775,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (BUF ? 5 : 1) : 3)
   if (chunk == 0 && (rhsw || wave == 0)) {   // (a right-hand-side wave: its own pair)
 #pragma unroll
     for (int row = lane; row < NPAD; row += 64) {
-      T* yz = Y + (int64_t)row * NVY + y_zero_run(sub.nH);
+      T* yz = Y + (int64_t)row * NVY + NVY - 16;
 #pragma unroll
       for (int i = 0; i < 16; ++i) yz[i] = T(0);
     }
@@ -1001,25 +1018,47 @@ __device__ __forceinline__ void stage_lds(T* __restrict__ dst, const T* __restri
 // a per-lane byte offset of the subdomain's node plus a uniform offset per slot, with no
 // 64-bit address arithmetic (FP64 measured 58.5 -> 53.8 us for condensation and
 // pull/extend at 128^3, FP32 unchanged; results bit for bit the same).
-template <typename T, bool BUF>
-__global__ void __launch_bounds__(64) k_sm_condense(const T* __restrict__ r, T* __restrict__ gg,
-                                                    const T* __restrict__ XT, DGeom g, int nH, Bat bt, int nbx,
-                                                    int packed) {
-  constexpr int NB = 48;
-  __shared__ T sX[6 * NB];
+// BOX (coefficient boxes): the block's lanes take subdomains of one box; X_T of that box and
+// of its 7 lower neighbours sit in LDS, and a lane at the lower faces of its box reads its
+// T - q from the neighbour's block.  256 lanes share the 8 blocks (9 / 18 KB).
+template <typename T, bool BUF, bool BOX>
+__global__ void __launch_bounds__(BOX ? 256 : 64) k_sm_condense(const T* __restrict__ r, T* __restrict__ gg,
+                                                                const T* __restrict__ XT, DGeom g, DSub sub, Bat bt,
+                                                                int nbx, int packed) {
+  constexpr int NB = 48, NXB = 6 * NB + (BOX ? 2 : 0);   // (2: spreads the blocks over the banks)
+  __shared__ T sX[(BOX ? 8 : 1) * NXB];
   const int3 bk = xcd_grid_block();
   const int pair = bk.x / nbx;
   if (inactive(bt, pair)) return;
-  XT += (int64_t)(pair / bt.nrhs) * 6 * NB;
-  // X_T's loads first, then this thread's residual loads, then X_T into LDS and the
-  // barrier: the residual loads are in flight across the staging (lanes past the box
-  // load subdomain 0's values and return after the barrier)
-  constexpr int RX = (6 * NB + 63) / 64;
+  int a, b, c, xs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  bool valid;
+  constexpr int RX = BOX ? (8 * 6 * NB) / 256 : (6 * NB + 63) / 64;
   T xv[RX];
-  stage_load(xv, XT, 6 * NB);
-  int a, b, c;
-  const bool valid = box_position(bk, nH, nbx, packed, a, b, c);
-  if (!valid) a = b = c = 0;
+  const int nH = sub.nH;
+  if constexpr (BOX) {
+    int o[3];
+    const int box = box_subdomain(bk.x % nbx, sub.r, sub.w, a, b, c, o, valid);
+    if (!(bt.coef[box] > 0.0)) return;   // outside the domain: no unknown here
+    const int bx = box % sub.r, by = (box / sub.r) % sub.r, bz = box / (sub.r * sub.r);
+#pragma unroll
+    for (int i = 0; i < RX; ++i) {
+      const int e = threadIdx.x + 256 * i, q = e / (6 * NB);
+      const int nbr = (max(bz - (q >> 2), 0) * sub.r + max(by - ((q >> 1) & 1), 0)) * sub.r + max(bx - (q & 1), 0);
+      xv[i] = XT[(int64_t)nbr * 6 * NB + e - q * 6 * NB];
+    }
+    // block of T - q: a step across a lower face of the box, per axis of q
+    const int f = (o[0] == 0) + 2 * (o[1] == 0) + 4 * (o[2] == 0);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) xs[q] = (q & f) * NXB;
+  } else {
+    XT += (int64_t)(pair / bt.nrhs) * 6 * NB;
+    // X_T's loads first, then this thread's residual loads, then X_T into LDS and the
+    // barrier: the residual loads are in flight across the staging (lanes past the box
+    // load subdomain 0's values and return after the barrier)
+    stage_load(xv, XT, 6 * NB);
+    valid = box_position(bk, nH, nbx, packed, a, b, c);
+    if (!valid) a = b = c = 0;
+  }
   const int64_t voff = (int64_t)pair * vlen(g);
   r += voff;
   gg += voff;
@@ -1070,7 +1109,15 @@ __global__ void __launch_bounds__(64) k_sm_condense(const T* __restrict__ r, T* 
     for (int k = 0; k < 18; ++k)
       rO[k] = r[kOI.d[k] * g.B + base + lin(g, kOI.o[k][0], kOI.o[k][1], kOI.o[k][2])];
   }
-  stage_store(sX, xv, 6 * NB);
+  if constexpr (BOX) {
+#pragma unroll
+    for (int i = 0; i < RX; ++i) {
+      const int e = threadIdx.x + 256 * i, q = e / (6 * NB);
+      sX[q * NXB + e - q * 6 * NB] = xv[i];
+    }
+  } else {
+    stage_store(sX, xv, 6 * NB);
+  }
   __syncthreads();
   if (!valid) return;
 #pragma unroll
@@ -1084,7 +1131,7 @@ __global__ void __launch_bounds__(64) k_sm_condense(const T* __restrict__ r, T* 
       if (m < kOI.nadj[k]) {
         const int qq = kOI.q[k][m], e = kOI.e[k][m];
 #pragma unroll
-        for (int t = 0; t < 6; ++t) acc -= sX[t * NB + e] * rI[qq][t];
+        for (int t = 0; t < 6; ++t) acc -= sX[xs[qq] + t * NB + e] * rI[qq][t];
       }
     }
     gg[off] = is_unknown(g, d, gi, gj, gk) ? acc : T(0);
@@ -1100,7 +1147,10 @@ __global__ void __launch_bounds__(64) k_sm_condense(const T* __restrict__ r, T* 
 // is written exactly once and w never goes to memory.  Edges on the domain boundary sum
 // to zero (their slots are absent from every patch that lists them).  All table lookups
 // are compile-time constants, so the 160 loads of a thread go out together.
-template <typename T>
+// BOX (coefficient boxes): the lanes take subdomains of one box, whose X_T and A_T^{-1} they
+// share; a corner's row position is its class triple's base (27 of them around a box) plus
+// its place in the class.
+template <typename T, bool BOX>
 __global__ void __launch_bounds__(64) k_sm_pull_extend(const T* __restrict__ Y, const T* __restrict__ r,
                                                        T* __restrict__ z, const T* __restrict__ XT,
                                                        const T* __restrict__ ATinv, DGeom g, DSub sub, T eta,
@@ -1117,8 +1167,14 @@ __global__ void __launch_bounds__(64) k_sm_pull_extend(const T* __restrict__ Y, 
   // staged in LDS (read in place, the compiler keeps too many of them in registers).
   // (k_sm_condense stages them: its products interleave with the loads, and scalar
   // loads on demand there measured slower.)
-  const T* __restrict__ gX = XT + (int64_t)(pair / bt.nrhs) * 6 * NB;
-  const T* __restrict__ gA = ATinv + (int64_t)(pair / bt.nrhs) * 36;
+  int a, b, c, ob[3] = {0, 0, 0}, box = 0;
+  bool valid;
+  if constexpr (BOX) {
+    box = box_subdomain(bk.x % nbx, sub.r, sub.w, a, b, c, ob, valid);
+    if (!(bt.coef[box] > 0.0)) return;   // outside the domain: no unknown here
+  }
+  const T* __restrict__ gX = XT + (int64_t)(BOX ? box : pair / bt.nrhs) * 6 * NB;
+  const T* __restrict__ gA = ATinv + (int64_t)(BOX ? box : pair / bt.nrhs) * 36;
   if constexpr (!kInPlace) {
     stage_lds<T, (6 * NB + 63) / 64>(lX, gX, 6 * NB);
     stage_lds<T, 1>(lA, gA, 36);
@@ -1133,9 +1189,9 @@ __global__ void __launch_bounds__(64) k_sm_pull_extend(const T* __restrict__ Y, 
     else return lA[i];
   };
   const int nH = sub.nH;
-  int a, b, c;
-  if (!box_position(bk, nH, nbx, packed, a, b, c)) return;
-  const int64_t NVY = y_row_len(nH);
+  if constexpr (!BOX) valid = box_position(bk, nH, nbx, packed, a, b, c);
+  if (!valid) return;
+  const int64_t NVY = sub.yrow;
   const int64_t voff = (int64_t)pair * vlen(g);
   r += voff;
   z += voff;
@@ -1146,8 +1202,25 @@ __global__ void __launch_bounds__(64) k_sm_pull_extend(const T* __restrict__ Y, 
   unsigned cb[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    const int x = a + (q & 1), y = b + ((q >> 1) & 1), zc = c + (q >> 2);
-    cb[q] = (unsigned)y_pos(nH, sub.bpatch, x, y, zc) * (unsigned)sizeof(T);
+    if constexpr (BOX) {
+      const int K = 2 * sub.r + 1, w = sub.w;
+      const int u[3] = {ob[0] + (q & 1), ob[1] + ((q >> 1) & 1), ob[2] + (q >> 2)};   // 0 .. w in the box
+      const int bx[3] = {box % sub.r, (box / sub.r) % sub.r, box / (sub.r * sub.r)};
+      int cl[3], lo[3], dm[3];
+#pragma unroll
+      for (int ax = 0; ax < 3; ++ax) {
+        const int in = (u[ax] > 0) & (u[ax] < w);
+        cl[ax] = 2 * bx[ax] + in + 2 * (u[ax] == w);
+        lo[ax] = in * (u[ax] - 1);
+        dm[ax] = 1 + in * (w - 2);
+      }
+      const int base = sub.cls[2 * ((cl[2] * K + cl[1]) * K + cl[0])];
+      const int local = lo[0] + dm[0] * (lo[1] + dm[1] * lo[2]);
+      cb[q] = (unsigned)(base + (base < (int)NVY - 16 ? local : 0)) * (unsigned)sizeof(T);
+    } else {
+      const int x = a + (q & 1), y = b + ((q >> 1) & 1), zc = c + (q >> 2);
+      cb[q] = (unsigned)y_pos(nH, sub.bpatch, x, y, zc) * (unsigned)sizeof(T);
+    }
   }
   const int64_t base = lin(g, 2 * a, 2 * b, 2 * c);
   int64_t ioff[6];
@@ -2143,7 +2216,7 @@ bool smoother_buffers(const DGeom& dg, const DSub& sub, const Bat& bt, size_t el
   int bits = 32, unused = 0;
   tune_lookup(kTunePatchAddr, dg.n, (int)elem, 0, bt.count, &bits, &unused);
   return bits == 32 && 3 * dg.B * (int64_t)elem < 0x7fffffffLL &&
-         y_row_len(sub.nH) * NPAD * (int64_t)elem < 0x7fffffffLL;
+         sub.yrow * NPAD * (int64_t)elem < 0x7fffffffLL;
 }
 
 template <typename T>
@@ -2161,18 +2234,32 @@ hipError_t launch_smooth(const T* r, T* z, const LevelPtrs<T>& L, const DSub& su
                          const Geom& g, const Bat& bt, double eta, int assign, hipStream_t st) {
   if (sub.s != 2) return hipErrorInvalidValue;
   const DGeom dg = dgeom(g);
-  // condensed interface residual gg = r - A A_T^{-1} r_I on the interface unknowns
   // rows shorter than a wave: lanes packed over the subdomain plane
   const int packed = (sub.nH < 64) ? 1 : 0;
   const int nbs = packed ? (sub.nH * sub.nH + 63) / 64 : (sub.nH + 63) / 64;
   const dim3 eg((unsigned)(nbs * bt.count), (unsigned)sub.nH, packed ? 1u : (unsigned)sub.nH);
-  if (smoother_buffers(dg, sub, bt, sizeof(T)))
-    hipLaunchKernelGGL((k_sm_condense<T, true>), eg, dim3(64), 0, st, r, L.gg, L.XT, dg, sub.nH, bt, nbs, packed);
+  // with coefficient boxes: blocks of subdomains of one box each
+  const int w3 = sub.w * sub.w * sub.w, nbox = sub.r * sub.r * sub.r;
+  const int nbc = nbox * ((w3 + 255) / 256), nbp = nbox * ((w3 + 63) / 64);
+  const bool buf = smoother_buffers(dg, sub, bt, sizeof(T));
+  // condensed interface residual gg = r - A A_T^{-1} r_I on the interface unknowns
+  if (sub.r > 0 && buf)
+    hipLaunchKernelGGL((k_sm_condense<T, true, true>), dim3((unsigned)(nbc * bt.count)), dim3(256), 0, st, r, L.gg,
+                       L.XT, dg, sub, bt, nbc, 0);
+  else if (sub.r > 0)
+    hipLaunchKernelGGL((k_sm_condense<T, false, true>), dim3((unsigned)(nbc * bt.count)), dim3(256), 0, st, r, L.gg,
+                       L.XT, dg, sub, bt, nbc, 0);
+  else if (buf)
+    hipLaunchKernelGGL((k_sm_condense<T, true, false>), eg, dim3(64), 0, st, r, L.gg, L.XT, dg, sub, bt, nbs, packed);
   else
-    hipLaunchKernelGGL((k_sm_condense<T, false>), eg, dim3(64), 0, st, r, L.gg, L.XT, dg, sub.nH, bt, nbs, packed);
+    hipLaunchKernelGGL((k_sm_condense<T, false, false>), eg, dim3(64), 0, st, r, L.gg, L.XT, dg, sub, bt, nbs, packed);
   if (sub.nchunks > 0) launch_sm_patch<T>(L, sub, dg, bt, st);
-  hipLaunchKernelGGL((k_sm_pull_extend<T>), eg, dim3(64), 0, st, L.Y, r, z, L.XT, L.ATinv, dg, sub, (T)eta, assign,
-                     bt, nbs, packed);
+  if (sub.r > 0)
+    hipLaunchKernelGGL((k_sm_pull_extend<T, true>), dim3((unsigned)(nbp * bt.count)), dim3(64), 0, st, L.Y, r, z, L.XT,
+                       L.ATinv, dg, sub, (T)eta, assign, bt, nbp, 0);
+  else
+    hipLaunchKernelGGL((k_sm_pull_extend<T, false>), eg, dim3(64), 0, st, L.Y, r, z, L.XT, L.ATinv, dg, sub, (T)eta,
+                       assign, bt, nbs, packed);
   return hipGetLastError();
 }
 

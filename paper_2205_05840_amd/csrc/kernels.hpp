@@ -54,6 +54,13 @@ struct DSub {
                         // between a wave's groups (all multiples of 16)
   int nchunks;
   const int64_t* bofs;  // nB offsets of the subdomain boundary edges from its lower node
+  int64_t yrow;         // row length of Y (its last 16 entries the zero run)
+  int ntypes;           // S^{-1} matrices per problem
+  // coefficient boxes: r per axis of w subdomains each (r = 0: none); cls [2 r + 1]^3 pairs
+  // {row position, type} per class triple of vertices (BoxPatches); A_T^{-1} and X_T then
+  // hold one block per box (zero outside the domain)
+  int r, w;
+  const int* cls;
 };
 
 // ---- Y, the vertex patch results of the large-level smoother --------------------------
@@ -114,9 +121,9 @@ struct LevelPtrs {
   T* w;       // interface correction (only interface entries ever written)
   T* Y;       // vertex patch results, [npad][y_row_len(nH)] per pair (the small-level
               // kernel uses [npad][(nH+1)^3] in the same buffer)
-  const T* ATinv;   // nI x nI per problem
-  const T* Sinv;    // 27 x npad x npad per problem
-  const T* XT;      // nI x nB per problem
+  const T* ATinv;   // nI x nI per problem (and per box)
+  const T* Sinv;    // ntypes x npad x npad per problem
+  const T* XT;      // nI x nB per problem (and per box)
 };
 
 int stencil_max_n();

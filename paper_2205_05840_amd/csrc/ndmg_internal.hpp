@@ -163,6 +163,26 @@ struct CoefBoxes {
   }
 };
 
+// Vertex patches of a level (s = 2) with coefficient boxes.  Along an axis the vertices fall
+// into 2 r + 1 classes: even class 2 q the one on the plane between the boxes q - 1 and q (0
+// and 2 r: the faces of the cube), odd class 2 q + 1 the w - 1 inside box q (w = nH / r
+// subdomains per box).  The vertices of one class triple form a box of the vertex grid and
+// share a patch type, as the 27 position types do without boxes (r = 1).
+struct BoxPatches {
+  int r = 0, w = 0;
+  std::vector<Segment> segs;           // class triples with patches; type: index below
+  std::vector<int> segY;               // row position of a segment's first vertex in Y
+  std::vector<int> cls;                // [2 r + 1]^3 (x fastest): {row position, or the zero run
+                                       // where there is no patch; type}
+  int64_t yrow = 0;                    // row length of Y; its last 16 entries are the zero run
+  // per type (0: no patch, a zero matrix): geometric type, factors of the 8 subdomains around
+  // the vertex (0 outside the domain), slots present
+  std::vector<int> geom;
+  std::vector<std::array<double, 8>> key;
+  std::vector<std::vector<char>> present;
+};
+bool build_box_patches(const Geom& g, bool boundary, const CoefBoxes& cf, BoxPatches* out, std::string* err);
+
 struct GenTables {
   int kind = 0, s = 2, ntypes = 27;
   // subdomain types: one per box of the coefficient (one without boxes), with its factor

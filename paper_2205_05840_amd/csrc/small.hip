@@ -17,12 +17,13 @@
 //                     restrict, then the weighted sums.
 // All loads that do not depend on one another go out before the first wait, the convergence
 // flag's among them (tested before the first store).  What bounds them is latency: launch,
-// one or two round trips and the LDS phases.  Measured at 16^3 / 32^3 in FP32: 4.9 / 9.0 us
-// for prolongation, residual, condensation and patch products (separate kernels 19 / 20), 3.4
-// / 4.0 for the interface sum (7), 3.5 / 4.8 for residual and restriction (9).  A level takes
-// 5 launches instead of 10.  One wavefront per vertex instead of a block measured slower (6.9
-// us at 10^3: about 900 instructions one after another); so did the condensed residual as a
-// launch of its own before the MFMA patch products at every size.
+// one or two round trips and the LDS phases.  Measured at 16^3 in FP32: 5.8 us for
+// prolongation, residual, condensation and patch products (separate kernels 19), 4.6 for
+// condensation and patch products (10), 3.5 for the interface sum (7), 3.9 for residual and
+// restriction (9).  A level takes 5 launches instead of 10.  One wavefront per vertex instead
+// of a block measured slower (6.9 us at 10^3: about 900 instructions one after another); so
+// did the condensed residual as a launch of its own before the MFMA patch products at every
+// size.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -48,12 +49,23 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
 // keeps the loads above it from sinking below a branch
 __device__ __forceinline__ void issue_barrier() { __asm__ volatile("" ::: "memory"); }
 
-// The cube of a vertex V: the nodes 2 V - 2 .. 2 V + 2 of each axis, an array [3][5][5][5]
-// of edges by their first node.  Wave d of a block works on the edges of direction d, so that
-// every stride is a constant.
-constexpr int kCube = 125;
+// The cube of a block: the nodes around its vertices, 2 V - 2 .. 2 V + 2 of each axis (one
+// vertex, CX = 5 nodes along x; two neighbours along x, CX = 7), an array [3][5][5][CX] of
+// edges by their first node.
+template <int CX>
+struct CubeShape {
+  static constexpr int N = 25 * CX;                       // entries per direction
+  static constexpr int st[3] = {1, CX, 5 * CX};
+  static __device__ __forceinline__ int at(int x, int y, int z) { return x + CX * y + 5 * CX * z; }
+  static __device__ __forceinline__ void pos(int m, int& x, int& y, int& z) {
+    z = m / (5 * CX);
+    const int q = m - z * 5 * CX;
+    y = q / CX;
+    x = q - y * CX;
+  }
+};
 
-// Lower node of the cube of a vertex, and the position of a lane's entries in it.
+// Lower node of a cube in the level.
 struct Cube {
   int x0, y0, z0, n;
   __device__ __forceinline__ bool inside(int x, int y, int z) const {
@@ -65,30 +77,24 @@ struct Cube {
   }
 };
 
-// entries lane and lane + 64 of direction d of v on the cube; 0 outside [0, n]^3
-template <typename T>
-__device__ __forceinline__ void load_cube(const T* __restrict__ v, const DGeom& g, const Cube& q, int d, int lane,
-                                          T (&out)[2]) {
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int m = min(lane + 64 * i, kCube - 1);
-    const int z = m / 25, m2 = m - z * 25, y = m2 / 5, x = m2 - y * 5;
-    const bool ok = q.inside(x, y, z);
-    const T t = v[ok ? d * g.B + lin(g, q.x0 + x, q.y0 + y, q.z0 + z) : 0];
-    out[i] = ok ? t : T(0);
-  }
+// entry m of direction d of v on the cube; 0 outside [0, n]^3
+template <int CX, typename T>
+__device__ __forceinline__ T load_cube(const T* __restrict__ v, const DGeom& g, const Cube& q, int d, int m) {
+  int x, y, z;
+  CubeShape<CX>::pos(m, x, y, z);
+  const bool ok = q.inside(x, y, z);
+  const T t = v[ok ? d * g.B + lin(g, q.x0 + x, q.y0 + y, q.z0 + z) : 0];
+  return ok ? t : T(0);
 }
 
-// (A u)_e at the edge of direction D whose first node is position p of the cube in LDS: the
-// factorised form alpha h C^T M_F C + h^3 M_E, the 33 entries read once
-template <int D, typename T>
-__device__ __forceinline__ T apply_cube(const T* L, int p, T ah, T h3) {
-  constexpr int st[3] = {1, 5, 25};
-  constexpr int sa = st[D], sb = st[(D + 1) % 3], sc = st[(D + 2) % 3];
-  const T* ua = L + D * kCube + p;
-  const T* ub = L + (D + 1) % 3 * kCube + p;
-  const T* uc = L + (D + 2) % 3 * kCube + p;
-  const T t6 = T(1) / T(6), t23 = T(2) / T(3);
+// (A u)_e at an edge of direction a: ua, ub, uc its entry and those of the next two
+// directions at its first node in LDS, sa, sb, sc the strides along and across it.  The
+// factorised form alpha h C^T M_F C + h^3 M_E, the 33 entries read once; COEF: c_{db dc} the
+// factors of the cells at -1 + db, -1 + dc across.
+template <bool COEF, typename T>
+__device__ __forceinline__ T apply_lds(const T* ua, const T* ub, const T* uc, int sa, int sb, int sc, T ah, T h3, T c00,
+                                       T c10, T c01, T c11) {
+  const T t6 = T(1) / T(6), t23 = T(2) / T(3), t3 = T(1) / T(3);
   T A[3][3], Ub[2][3][2], Uc[2][3][2];   // offsets [b][c]; [b: -1, 0][c][a]; [c: -1, 0][b][a]
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -112,11 +118,18 @@ __device__ __forceinline__ T apply_cube(const T* L, int p, T ah, T h3) {
       Fb[i][j] = (A[j][i + 1] - A[j][i]) - (Uc[i][j][1] - Uc[i][j][0]);
       Fc[i][j] = (Ub[i][j][1] - Ub[i][j][0]) - (A[i + 1][j] - A[i][j]);
     }
+  // a face between the cells of factors m (below along its normal) and p
+  const T bm[2] = {c00, c01}, bp[2] = {c10, c11}, cm[2] = {c00, c10}, cp[2] = {c01, c11};
   T Gb[2], Gc[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    Gb[i] = t6 * (Fb[i][0] + Fb[i][2]) + t23 * Fb[i][1];
-    Gc[i] = t6 * (Fc[i][0] + Fc[i][2]) + t23 * Fc[i][1];
+    if constexpr (COEF) {
+      Gb[i] = t6 * (bm[i] * Fb[i][0] + bp[i] * Fb[i][2]) + t3 * (bm[i] + bp[i]) * Fb[i][1];
+      Gc[i] = t6 * (cm[i] * Fc[i][0] + cp[i] * Fc[i][2]) + t3 * (cm[i] + cp[i]) * Fc[i][1];
+    } else {
+      Gb[i] = t6 * (Fb[i][0] + Fb[i][2]) + t23 * Fb[i][1];
+      Gc[i] = t6 * (Fc[i][0] + Fc[i][2]) + t23 * Fc[i][1];
+    }
   }
   const T curl = (Gb[0] - Gb[1]) - (Gc[0] - Gc[1]);
   T row[3];
@@ -125,47 +138,84 @@ __device__ __forceinline__ T apply_cube(const T* L, int p, T ah, T h3) {
   const T mass = t6 * (row[0] + row[2]) + t23 * row[1];
   return ah * curl + h3 * mass;
 }
+// the same at position p of direction D of a cube, every stride a constant
+template <int D, int CX, bool COEF, typename T>
+__device__ __forceinline__ T apply_cube(const T* L, int p, T ah, T h3, T c00, T c10, T c01, T c11) {
+  using S = CubeShape<CX>;
+  return apply_lds<COEF>(L + D * S::N + p, L + (D + 1) % 3 * S::N + p, L + (D + 2) % 3 * S::N + p, S::st[D],
+                         S::st[(D + 1) % 3], S::st[(D + 2) % 3], ah, h3, c00, c10, c01, c11);
+}
 
-// Position of an edge of direction d at offset a along it and b, c across (axes d + 1, d + 2).
+// Coefficient boxes: the factor of cell m of a cube (CX - 1 cells along x, 4 x 4 across), 0
+// outside the level (and in the boxes outside a domain: no unknown touches such a cell).
+template <int CX>
+__device__ __forceinline__ double load_cell(const Bat& bt, const Cube& q, const BoxDiv& dv, int m) {
+  const int cz = m / (4 * (CX - 1)), cq = m - cz * 4 * (CX - 1), cy = cq / (CX - 1), cx = cq - cy * (CX - 1);
+  const int x = q.x0 + cx, y = q.y0 + cy, z = q.z0 + cz;
+  const bool ok = (unsigned)x < (unsigned)q.n && (unsigned)y < (unsigned)q.n && (unsigned)z < (unsigned)q.n;
+  const int r = bt.coef_r;
+  const double f = bt.coef[ok ? (dv.box(z >> 1) * r + dv.box(y >> 1)) * r + dv.box(x >> 1) : 0];
+  return ok ? f : 0.0;
+}
+
 struct Pos {
   int x, y, z;
-  __device__ __forceinline__ int lin() const { return x + 5 * y + 25 * z; }
 };
+// edge of direction d at offset a along it and b, c across (axes d + 1, d + 2)
 __device__ __forceinline__ Pos edge_pos(int d, int a, int b, int c) {
   return d == 0 ? Pos{a, b, c} : (d == 1 ? Pos{c, a, b} : Pos{b, c, a});
 }
+// factors of the four cells around the edge of direction d at p, from the cube's cells
+template <int CX, typename T>
+__device__ __forceinline__ void edge_cells(const T* fL, int d, const Pos& p, T& c00, T& c10, T& c01, T& c11) {
+  const int cell = p.x + (CX - 1) * (p.y + 4 * p.z);
+  const int sx = 1, sy = CX - 1, sz = 4 * (CX - 1);
+  const int sb = d == 0 ? sy : (d == 1 ? sz : sx), sc = d == 0 ? sz : (d == 1 ? sx : sy);
+  c00 = fL[cell - sb - sc];
+  c10 = fL[cell - sc];
+  c01 = fL[cell - sb];
+  c11 = fL[cell];
+}
 
 // I zc at the edge of direction D at cube node (x, y, z), from the coarse cube cL
-// ([3][3][3][3], coarse nodes V - 1 .. V + 1): weight 1/2 each side across an axis at an odd
-// offset (the cube's lower node is even)
-template <int D, typename T>
+// ([3][3][3][CC], from the node half the cube's lower node): weight 1/2 each side across an
+// axis at an odd offset (the cube's lower node is even)
+template <int D, int CC, typename T>
 __device__ __forceinline__ T prolong_cube(const T* cL, int x, int y, int z) {
   const int o[3] = {x, y, z};
-  constexpr int st[3] = {1, 3, 9};
+  constexpr int st[3] = {1, CC, 3 * CC};
   const int ob = o[(D + 1) % 3] & 1, oc = o[(D + 2) % 3] & 1;
   const int sb = ob * st[(D + 1) % 3], sc = oc * st[(D + 2) % 3];
-  const T* e = cL + 27 * D + (x >> 1) + 3 * (y >> 1) + 9 * (z >> 1);
+  const T* e = cL + 9 * CC * D + (x >> 1) + CC * (y >> 1) + 3 * CC * (z >> 1);
   const T wb0 = ob ? T(0.5) : T(1), wb1 = ob ? T(0.5) : T(0);
   const T wc0 = oc ? T(0.5) : T(1), wc1 = oc ? T(0.5) : T(0);
   const T lo = wb0 * e[0] + wb1 * e[sb], hi = wb0 * e[sc] + wb1 * e[sb + sc];
   return wc0 * lo + wc1 * hi;
 }
 
-// One block per vertex V.  MODE 0: r = g; 1: r = g - A z; 2: r = g - A (z + I zc).
-template <typename T, int MODE>
+// One block per NV vertices V, V + e_x (NV = 2: the pairs (2 p - 1, 2 p), which share their
+// cube's residuals and, inside a type's range, S^{-1}; a pair's vertex outside 0 .. nH is
+// computed from zeros and not stored).  Wave d < 3 works on the edges of direction d.
+// MODE 0: r = g; 1: r = g - A z; 2: r = g - A (z + I zc).  COEF: coefficient boxes, with the
+// patch type from the vertex's class triple (BoxPatches) and X_T from each subdomain's box.
+template <typename T, int MODE, bool COEF, int NV>
 __global__ void __launch_bounds__(256) k_small_patch(const T* __restrict__ g, const T* __restrict__ z,
                                                      const T* __restrict__ zc, SmallSub<T> s, DGeom gc, Bat bt) {
   constexpr int NG = 60, NPAD = 64, NX = 288, NC = NG / 4;
-  __shared__ T zL[MODE ? 3 * kCube : 1];
-  __shared__ T rL[3 * kCube];
-  __shared__ T cL[MODE == 2 ? 81 : 1];
-  __shared__ T xL[NX];
-  __shared__ __attribute__((aligned(16))) T gL[NPAD];
-  __shared__ T pL[4][NPAD];
-  const int nv = s.nH + 1, nv3 = nv * nv * nv;
+  constexpr int CX = 3 + 2 * NV, CC = 2 + NV;
+  using S = CubeShape<CX>;
+  constexpr int NL = (S::N + 63) / 64, NF = (16 * (CX - 1) + 63) / 64;
+  __shared__ T zL[MODE ? 3 * S::N : 1];
+  __shared__ T rL[3 * S::N];
+  __shared__ T cL[MODE == 2 ? 27 * CC : 1];
+  __shared__ T xL[COEF ? 1 : NX];
+  __shared__ T fL[COEF ? 64 * NF : 1];
+  __shared__ T gL[NV][NPAD];
+  __shared__ T pL[NV][4][NPAD];
+  const int nv = s.nH + 1, nv3 = nv * nv * nv, nb = NV == 1 ? nv : nv / 2 + 1;
   const int lb = xcd_block(blockIdx.x, gridDim.x);
-  const int pair = lb / nv3, v = lb - pair * nv3;
-  const int vx = v % nv, vy = (v / nv) % nv, vz = v / (nv * nv);
+  const int pair = lb / (nb * nv * nv), v = lb - pair * (nb * nv * nv);
+  const int vx = NV == 1 ? v % nb : 2 * (v % nb) - 1, vy = (v / nb) % nv, vz = v / (nb * nv);
   const int act = bt.act ? bt.act[pair] : 1;
   const int prob = pair / bt.nrhs;
   const T ah = MODE ? (T)(bt.alpha[prob] * s.h) : T(0);
@@ -173,68 +223,114 @@ __global__ void __launch_bounds__(256) k_small_patch(const T* __restrict__ g, co
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t off = (int64_t)pair * 3 * s.g.B;
   const Cube q{2 * vx - 2, 2 * vy - 2, 2 * vz - 2, s.g.n};
-  T zv[2], cv = T(0), gv = T(0), xv[5], sv[NC];
-  // this lane's inner edge of direction `wave`: offset 0 .. 3 along it, nodes 1 .. 3 across
-  const int il = min(lane, 35);
-  const Pos ip = edge_pos(wave, il & 3, 1 + (il >> 2) % 3, 1 + il / 12);
+  T zv[NL], cv = T(0), gv = T(0), xv[COEF ? 6 * NV : 5], sv[NC];
+  double fv[NF];
+  // condensation: four lanes per slot, one subdomain each
+  const uint32_t* __restrict__ tab = s.tab + kSmallSlots + 5 * min(tid >> 2, NG - 1);
+  const uint32_t slot = tab[0], code = tab[1 + (tid & 3)];
+  // patch type of vertex j
+  auto type_of = [&](int j) {
+    const int x = min(max(vx + j, 0), s.nH);
+    if constexpr (COEF) {
+      const int K = 2 * bt.coef_r + 1;
+      auto cls = [&](int u) {
+        const int b = s.dv.box(u);
+        return 2 * b + (u != b * s.dv.w ? 1 : 0);
+      };
+      return s.cls[2 * ((cls(vz) * K + cls(vy)) * K + cls(x)) + 1];
+    } else {
+      return (x == 0 ? 0 : (x == s.nH ? 2 : 1)) + 3 * (vy == 0 ? 0 : (vy == s.nH ? 2 : 1)) +
+             9 * (vz == 0 ? 0 : (vz == s.nH ? 2 : 1));
+    }
+  };
+  int type[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) type[j] = type_of(j);
+  // this lane's inner edge of direction `wave`: nodes 1 .. 3 (along x: CX - 2) across it
+  const int nx = wave == 0 ? CX - 1 : CX - 2;           // positions along x
+  const int ninner = wave == 0 ? 9 * (CX - 1) : 12 * (CX - 2);
+  const int il = min(lane, ninner - 1);
+  const int ix = il % nx, iq = il / nx;
+  const Pos ip = wave == 0 ? Pos{ix, 1 + iq % 3, 1 + iq / 3}
+                           : (wave == 1 ? Pos{1 + ix, iq & 3, 1 + iq / 4} : Pos{1 + ix, 1 + iq % 3, iq / 3});
   const bool iu = wave < 3 && q.unknown(wave, ip.x, ip.y, ip.z);
   if (wave < 3) {
-    if constexpr (MODE != 0) load_cube(z + off, s.g, q, wave, lane, zv);
+    if constexpr (MODE != 0) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) zv[i] = load_cube<CX>(z + off, s.g, q, wave, min(lane + 64 * i, S::N - 1));
+    }
     if constexpr (MODE == 2) {
-      const int m = min(lane, 26), w = m / 9, y = m / 3 % 3, x = m % 3;
+      const int m = min(lane, 9 * CC - 1), w = m / (3 * CC), y = m / CC % 3, x = m % CC;
       const bool ok = (unsigned)(vx - 1 + x) <= (unsigned)gc.n && (unsigned)(vy - 1 + y) <= (unsigned)gc.n &&
                       (unsigned)(vz - 1 + w) <= (unsigned)gc.n;
       const T t = zc[(int64_t)pair * 3 * gc.B + (ok ? wave * gc.B + lin(gc, vx - 1 + x, vy - 1 + y, vz - 1 + w) : 0)];
       cv = ok ? t : T(0);
     }
     gv = g[off + (iu ? wave * s.g.B + lin(s.g, q.x0 + ip.x, q.y0 + ip.y, q.z0 + ip.z) : 0)];
+  } else if constexpr (COEF) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i) fv[i] = load_cell<CX>(bt, q, s.dv, min(lane + 64 * i, 16 * (CX - 1) - 1));
   } else {
 #pragma unroll
     for (int i = 0; i < 5; ++i) xv[i] = s.XT[(int64_t)prob * NX + min(lane + 64 * i, NX - 1)];
   }
-  // condensation: four lanes per slot, one subdomain each
-  const uint32_t* __restrict__ tab = s.tab + kSmallSlots + 5 * min(tid >> 2, NG - 1);
-  const uint32_t pos = tab[0], code = tab[1 + (tid & 3)];
-  const int type = (vx == 0 ? 0 : (vx == s.nH ? 2 : 1)) + 3 * (vy == 0 ? 0 : (vy == s.nH ? 2 : 1)) +
-                   9 * (vz == 0 ? 0 : (vz == s.nH ? 2 : 1));
+  // subdomain (of the 8 around a vertex) and boundary edge of this lane's condensation term
+  const bool on = code != 0xffff;
+  const int sx = code & 1, sy = (code >> 1) & 1, sz = (code >> 2) & 1, ce = on ? (int)(code >> 3) : 0;
+  if constexpr (COEF) {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      // (a subdomain outside the cube has no term: its slots are absent)
+      const int r = bt.coef_r, m = s.nH - 1;
+      const int a = min(max(vx + j - 1 + sx, 0), m), b = min(max(vy - 1 + sy, 0), m), c = min(max(vz - 1 + sz, 0), m);
+      const T* __restrict__ X = s.XT + ((s.dv.box(c) * r + s.dv.box(b)) * r + s.dv.box(a)) * NX + ce;
+#pragma unroll
+      for (int t = 0; t < 6; ++t) xv[6 * j + t] = X[t * 48];
+    }
+  }
   // S^{-1} is symmetric: column k of this lane's row is entry (k, lane); wave w takes the
   // columns 15 w .. 15 w + 14
-  const T* __restrict__ Sm = s.Sinv + prob * s.sstride + (int64_t)type * NPAD * NPAD + wave * NC * NPAD + lane;
+  auto load_s = [&](int ty) {
+    const T* __restrict__ Sm = s.Sinv + prob * s.sstride + (int64_t)ty * NPAD * NPAD + wave * NC * NPAD + lane;
 #pragma unroll
-  for (int k = 0; k < NC; ++k) sv[k] = Sm[k * NPAD];
+    for (int k = 0; k < NC; ++k) sv[k] = Sm[k * NPAD];
+  };
+  load_s(type[0]);
   issue_barrier();
   if (act == 0) return;
   if (wave == 3) {
+    if constexpr (COEF) {
 #pragma unroll
-    for (int i = 0; i < 5; ++i)
-      if (lane + 64 * i < NX) xL[lane + 64 * i] = xv[i];
+      for (int i = 0; i < NF; ++i) fL[lane + 64 * i] = (T)fv[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 5; ++i)
+        if (lane + 64 * i < NX) xL[lane + 64 * i] = xv[i];
+    }
   } else if constexpr (MODE == 0) {
-    if (lane < 36) rL[wave * kCube + ip.lin()] = iu ? gv : T(0);
-  } else {
-    if constexpr (MODE == 2) {
-      if (lane < 27) cL[27 * wave + lane] = cv;
-    }
-    if constexpr (MODE == 1) {
+    // (entries off the unknowns of a domain are zero in every residual)
+    if (lane < ninner) rL[wave * S::N + S::at(ip.x, ip.y, ip.z)] = iu ? gv : T(0);
+  } else if constexpr (MODE == 1) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        if (lane + 64 * i < kCube) zL[wave * kCube + lane + 64 * i] = zv[i];
-    }
-  }
-  if constexpr (MODE == 2) {
+    for (int i = 0; i < NL; ++i)
+      if (lane + 64 * i < S::N) zL[wave * S::N + lane + 64 * i] = zv[i];
+  } else {
+    if (lane < 9 * CC) cL[9 * CC * wave + lane] = cv;
     // (a wave prolongs its own direction from the coarse entries it has just written)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     auto prolong = [&](auto dir) {
       constexpr int D = decltype(dir)::value;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int m = min(lane + 64 * i, kCube - 1);
-        const int w = m / 25, m2 = m - w * 25, y = m2 / 5, x = m2 - y * 5;
+      for (int i = 0; i < NL; ++i) {
+        const int m = min(lane + 64 * i, S::N - 1);
+        int x, y, w;
+        S::pos(m, x, y, w);
         // (an entry past the last element along its direction is not an edge of the cube)
-        const T add = (D == 0 ? x : (D == 1 ? y : w)) < 4 ? prolong_cube<D>(cL, x, y, w) : T(0);
-        if (lane + 64 * i < kCube) zL[D * kCube + m] = zv[i] + add;
+        const T add = (D == 0 ? x < CX - 1 : (D == 1 ? y < 4 : w < 4)) ? prolong_cube<D, CC>(cL, x, y, w) : T(0);
+        if (lane + 64 * i < S::N) zL[D * S::N + m] = zv[i] + add;
       }
     };
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
     if (wave == 0) prolong(std::integral_constant<int, 0>{});
     if (wave == 1) prolong(std::integral_constant<int, 1>{});
     if (wave == 2) prolong(std::integral_constant<int, 2>{});
@@ -242,44 +338,56 @@ __global__ void __launch_bounds__(256) k_small_patch(const T* __restrict__ g, co
   __syncthreads();
   if constexpr (MODE != 0) {
     const T h3 = (T)(s.h * s.h * s.h);
-    const int p = ip.lin();
-    T ax = T(0);
-    if (wave == 0) ax = apply_cube<0>(zL, p, ah, h3);
-    if (wave == 1) ax = apply_cube<1>(zL, p, ah, h3);
-    if (wave == 2) ax = apply_cube<2>(zL, p, ah, h3);
-    if (wave < 3 && lane < 36) rL[wave * kCube + p] = iu ? gv - ax : T(0);
+    const int p = S::at(ip.x, ip.y, ip.z);
+    T ax = T(0), c00 = T(1), c10 = T(1), c01 = T(1), c11 = T(1);
+    if constexpr (COEF) edge_cells<CX>(fL, wave, ip, c00, c10, c01, c11);
+    if (wave == 0) ax = apply_cube<0, CX, COEF>(zL, p, ah, h3, c00, c10, c01, c11);
+    if (wave == 1) ax = apply_cube<1, CX, COEF>(zL, p, ah, h3, c00, c10, c01, c11);
+    if (wave == 2) ax = apply_cube<2, CX, COEF>(zL, p, ah, h3, c00, c10, c01, c11);
+    const bool in = iu && c00 > T(0) && c10 > T(0) && c01 > T(0) && c11 > T(0);
+    if (wave < 3 && lane < ninner) rL[wave * S::N + p] = in ? gv - ax : T(0);
     __syncthreads();
   }
-  T c = T(0);
   {
-    // interior unknown t of subdomain sd of the cube: a constant offset from its lower node
-    constexpr int io[6] = {30, 31, kCube + 26, kCube + 31, 2 * kCube + 6, 2 * kCube + 31};
-    const bool on = code != 0xffff;
-    const int sd = code & 7, e = on ? (int)(code >> 3) : 0;
-    const T* rq = rL + 2 * (sd & 1) + 10 * ((sd >> 1) & 1) + 50 * (sd >> 2);
+    // interior unknown t of a subdomain: a constant offset from its lower node
+    constexpr int io[6] = {6 * CX,             1 + 6 * CX,         S::N + 1 + 5 * CX,
+                           S::N + 1 + 6 * CX,  2 * S::N + 1 + CX,  2 * S::N + 1 + 6 * CX};
+    const int pos = (slot & 3) * S::N + S::at((slot >> 2) & 7, (slot >> 5) & 7, (slot >> 8) & 7);
+    const T* rs = rL + S::at(2 * sx, 2 * sy, 2 * sz);
 #pragma unroll
-    for (int t = 0; t < 6; ++t) c += xL[t * 48 + e] * rq[io[t]];
-    c = on ? c : T(0);
-  }
-  c += __shfl_xor(c, 1, 64);
-  c += __shfl_xor(c, 2, 64);
-  if constexpr (MODE != 0) {
-    // r on the interior of the subdomain whose lower corner is V
-    if (wave == 1 && lane < 6 && vx < s.nH && vy < s.nH && vz < s.nH) {
-      const int d = lane >> 1, f = lane & 1;   // (order of interior_dofs)
-      const int ex = d == 0 ? f : 1, ey = d == 1 ? f : 1, ez = d == 2 ? f : 1;
-      s.r[off + d * s.g.B + lin(s.g, 2 * vx + ex, 2 * vy + ey, 2 * vz + ez)] =
-          rL[d * kCube + (2 + ex) + 5 * (2 + ey) + 25 * (2 + ez)];
+    for (int j = 0; j < NV; ++j) {
+      T c = T(0);
+#pragma unroll
+      for (int t = 0; t < 6; ++t) c += (COEF ? xv[COEF ? 6 * j + t : 0] : xL[COEF ? 0 : t * 48 + ce]) * rs[2 * j + io[t]];
+      c = on ? c : T(0);
+      c += __shfl_xor(c, 1, 64);
+      c += __shfl_xor(c, 2, 64);
+      if ((tid & 3) == 0) gL[j][tid >> 2] = tid < 4 * NG ? rL[pos + 2 * j] - c : T(0);
     }
   }
-  if ((tid & 3) == 0) gL[tid >> 2] = tid < 4 * NG ? rL[pos] - c : T(0);
+  if constexpr (MODE != 0) {
+    // r on the interiors of the subdomains whose lower corners are the vertices
+    const int j = lane / 6, t = lane - 6 * j, a = vx + j;
+    if (wave == 1 && lane < 6 * NV && a >= 0 && a < s.nH && vy < s.nH && vz < s.nH) {
+      const int d = t >> 1, f = t & 1;   // (order of interior_dofs)
+      const int ex = d == 0 ? f : 1, ey = d == 1 ? f : 1, ez = d == 2 ? f : 1;
+      s.r[off + d * s.g.B + lin(s.g, 2 * a + ex, 2 * vy + ey, 2 * vz + ez)] =
+          rL[d * S::N + S::at(2 + 2 * j + ex, 2 + ey, 2 + ez)];
+    }
+  }
   __syncthreads();
-  T y = T(0);
 #pragma unroll
-  for (int k = 0; k < NC; ++k) y += sv[k] * gL[wave * NC + k];
-  pL[wave][lane] = y;
+  for (int j = 0; j < NV; ++j) {
+    if (j > 0 && type[j] != type[0]) load_s(type[j]);
+    T y = T(0);
+#pragma unroll
+    for (int k = 0; k < NC; ++k) y += sv[k] * gL[j][wave * NC + k];
+    pL[j][wave][lane] = y;
+  }
   __syncthreads();
-  if (wave == 0) s.Y[((int64_t)pair * nv3 + v) * NPAD + lane] = (pL[0][lane] + pL[1][lane]) + (pL[2][lane] + pL[3][lane]);
+  if (wave < NV && vx + wave >= 0 && vx + wave <= s.nH)
+    s.Y[((int64_t)pair * nv3 + (vz * nv + vy) * nv + vx + wave) * NPAD + lane] =
+        (pL[wave][0][lane] + pL[wave][1][lane]) + (pL[wave][2][lane] + pL[wave][3][lane]);
 }
 
 // Lane e < 48: boundary edge e of the subdomain; lanes 48 .. 53: its interior unknowns.
@@ -294,7 +402,9 @@ __global__ void __launch_bounds__(64) k_small_pull(const T* __restrict__ r, T* z
   const int pair = lb / ns, u = lb - pair * ns;
   const int a = u % nH, b = (u / nH) % nH, c = u / (nH * nH);
   const int act = bt.act ? bt.act[pair] : 1;
-  const int prob = pair / bt.nrhs;
+  // factors of the problem, or of the subdomain's box
+  int prob = pair / bt.nrhs;
+  if (bt.coef) prob = (s.dv.box(c) * bt.coef_r + s.dv.box(b)) * bt.coef_r + s.dv.box(a);
   const int lane = threadIdx.x;
   const int64_t off = (int64_t)pair * 3 * s.g.B;
   const uint32_t* __restrict__ tab = s.tab + kSmallEdges + 5 * min(lane, 53);
@@ -352,43 +462,57 @@ __global__ void __launch_bounds__(64) k_small_pull(const T* __restrict__ r, T* z
   if (mine && lane < 54) z[at] = (zo + pro) + (T)s.eta * (lane < 48 ? w : zi);
 }
 
-// Lane of wave d: offset 0 / 1 along the direction d, -1 .. 1 across, of the 18 fine edges
-// that the coarse edge of direction d at node V restricts.
-template <typename T>
-__global__ void __launch_bounds__(192) k_small_restrict(const T* __restrict__ g, const T* __restrict__ z,
-                                                        T* __restrict__ out, DGeom f, double h, DGeom c, Bat bt) {
-  __shared__ T zL[3 * kCube];
+// Lane: direction, offset 0 / 1 along it, -1 .. 1 across, of the 54 fine edges that the three
+// coarse edges of node V restrict.  (A wave per direction, with constant strides, measured
+// slower: 8.6 against 5.7 us at 32^3 in FP64, 4.4 against 3.9 at 16^3.)
+template <typename T, bool COEF>
+__global__ void __launch_bounds__(64) k_small_restrict(const T* __restrict__ g, const T* __restrict__ z,
+                                                       T* __restrict__ out, DGeom f, double h, DGeom c, BoxDiv dv,
+                                                       Bat bt) {
+  using S = CubeShape<5>;
+  constexpr int NL = (3 * S::N + 63) / 64;
+  __shared__ T zL[3 * S::N];
   __shared__ T rL[54];
+  __shared__ T fL[COEF ? 64 : 1];
   const int nc = c.n, nc3 = nc * nc * nc;
   const int lb = xcd_block(blockIdx.x, gridDim.x);
   const int pair = lb / nc3, v = lb - pair * nc3;
   const int vx = v % nc, vy = (v / nc) % nc, vz = v / (nc * nc);
   const int act = bt.act ? bt.act[pair] : 1;
   const T ah = (T)(bt.alpha[pair / bt.nrhs] * h), h3 = (T)(h * h * h);
-  const int lane = threadIdx.x & 63, d = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x;
   const int64_t off = (int64_t)pair * 3 * f.B;
   const Cube q{2 * vx - 2, 2 * vy - 2, 2 * vz - 2, f.n};
-  T zv[2];
-  load_cube(z + off, f, q, d, lane, zv);
-  const int l = min(lane, 17);
-  const Pos e = edge_pos(d, 2 + (l & 1), 1 + (l >> 1) % 3, 1 + l / 6);
+  T zv[NL];
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int m = min(lane + 64 * i, 3 * S::N - 1), d = m / S::N;
+    zv[i] = load_cube<5>(z + off, f, q, d, m - d * S::N);
+  }
+  const int l = min(lane, 53), d = l / 18, e18 = l - 18 * d;
+  const Pos e = edge_pos(d, 2 + (e18 & 1), 1 + (e18 >> 1) % 3, 1 + e18 / 6);
   const bool on = q.unknown(d, e.x, e.y, e.z);
   const T gv = g[off + (on ? d * f.B + lin(f, q.x0 + e.x, q.y0 + e.y, q.z0 + e.z) : 0)];
+  double fv = 0.0;
+  if constexpr (COEF) fv = load_cell<5>(bt, q, dv, lane);
   issue_barrier();
   if (act == 0) return;
+  if constexpr (COEF) fL[lane] = (T)fv;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-    if (lane + 64 * i < kCube) zL[d * kCube + lane + 64 * i] = zv[i];
+  for (int i = 0; i < NL; ++i)
+    if (lane + 64 * i < 3 * S::N) zL[lane + 64 * i] = zv[i];
   __syncthreads();
-  T ax = T(0);
-  if (d == 0) ax = apply_cube<0>(zL, e.lin(), ah, h3);
-  if (d == 1) ax = apply_cube<1>(zL, e.lin(), ah, h3);
-  if (d == 2) ax = apply_cube<2>(zL, e.lin(), ah, h3);
-  if (lane < 18) rL[18 * d + lane] = on ? gv - ax : T(0);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  if (lane == 0) {
-    const T* s = rL + 18 * d;
+  T c00 = T(1), c10 = T(1), c01 = T(1), c11 = T(1);
+  if constexpr (COEF) edge_cells<5>(fL, d, e, c00, c10, c01, c11);
+  const int sa = d == 0 ? 1 : (d == 1 ? 5 : 25), sb = d == 0 ? 5 : (d == 1 ? 25 : 1), sc = d == 0 ? 25 : (d == 1 ? 1 : 5);
+  const T* zp = zL + S::at(e.x, e.y, e.z);
+  const T ax = apply_lds<COEF>(zp + d * S::N, zp + (d == 2 ? 0 : d + 1) * S::N, zp + (d == 0 ? 2 : d - 1) * S::N, sa, sb,
+                               sc, ah, h3, c00, c10, c01, c11);
+  const bool in = on && c00 > T(0) && c10 > T(0) && c01 > T(0) && c11 > T(0);
+  if (lane < 54) rL[lane] = in ? gv - ax : T(0);
+  __syncthreads();
+  if (lane < 3) {
+    const T* s = rL + 18 * lane;
     T acc = T(0);
 #pragma unroll
     for (int k = 0; k < 2; ++k) {   // the two fine edges along the coarse one
@@ -397,8 +521,12 @@ __global__ void __launch_bounds__(192) k_small_restrict(const T* __restrict__ g,
       const T hi = T(0.5) * (s[k + 4] + s[k + 16]) + s[k + 10];
       acc += T(0.5) * (lo + hi) + mid;
     }
-    out[(int64_t)pair * 3 * c.B + d * c.B + lin(c, vx, vy, vz)] =
-        vx >= (d != 0) && vy >= (d != 1) && vz >= (d != 2) ? acc : T(0);
+    bool cin = vx >= (lane != 0) && vy >= (lane != 1) && vz >= (lane != 2);
+    if constexpr (COEF) {   // the coarse edge's cells are those around its first fine edge
+      edge_cells<5>(fL, lane, Pos{2, 2, 2}, c00, c10, c01, c11);
+      cin = cin && c00 > T(0) && c10 > T(0) && c01 > T(0) && c11 > T(0);
+    }
+    out[(int64_t)pair * 3 * c.B + lane * c.B + lin(c, vx, vy, vz)] = cin ? acc : T(0);
   }
 }
 
@@ -434,7 +562,7 @@ std::vector<uint32_t> make_tables() {
         if (bd[e].d == sl[i].d && 2 * (q & 1) + bd[e].dx == o[0] && 2 * ((q >> 1) & 1) + bd[e].dy == o[1] &&
             2 * (q >> 2) + bd[e].dz == o[2])
           codes.push_back((uint32_t)(q | (int)e << 3));
-    set(kSmallSlots + 5 * (int)i, (uint32_t)(sl[i].d * kCube + o[0] + 5 * o[1] + 25 * o[2]), codes);
+    set(kSmallSlots + 5 * (int)i, (uint32_t)(sl[i].d | o[0] << 2 | o[1] << 5 | o[2] << 8), codes);
   }
   return t;
 }
@@ -447,26 +575,50 @@ const std::vector<uint32_t>& small_tables() {
 }
 
 // Measured on MI355X (us per CG iteration of one problem, large-level kernels / these, the
-// levels below on these): 16^3 FP32 79 / 55, FP64 85 / 56; 24^3 97 / 79, 104 / 85; 32^3 105 /
-// 100, 119 / 115; 40^3 135 / 149, 157 / 183; 48^3 146 / 191.  The work grows with the
-// vertices of all pairs, each reading its own S^{-1} and repeating its neighbours' residuals,
-// while the large-level kernels' time below 32^3 is their round trips; the two cross between
-// 17^3 and 21^3 vertices.
+// levels below on these): 16^3 FP32 79 / 56, FP64 85 / 56; 24^3 97 / 78, 104 / 83; 32^3 105 /
+// 94, 119 / 107 (Fichera domain 117 / 101, 133 / 118); 40^3 135 / 134, 157 / 162; 48^3 146 /
+// 164.  The work grows with the vertices of all pairs, each reading its S^{-1} and repeating
+// its neighbours' residuals, while the large-level kernels' time below 32^3 is their round
+// trips; the two cross between 17^3 and 21^3 vertices.
 bool small_level(int nH, int count) {
   const int64_t nv = nH + 1;
   return nv * nv * nv * count <= 6000;
 }
 
+// Two vertices per block where the blocks outnumber the compute units: they share S^{-1}, whose
+// loads bound the launch from 24^3 on (32^3 FP64 107 against 116 us per iteration, 20^3 86 /
+// 88, equal at 16^3); with fewer vertices one per block (10^3 63 against 64).
+static bool small_pairs(int nH, int count) {
+  const int64_t nv = nH + 1;
+  return nv * nv * nv * count > 500;
+}
+
 template <typename T>
 hipError_t launch_small_patch(int mode, const T* g, const T* z, const T* zc, const SmallSub<T>& s, const DGeom& gc,
                               const Bat& bt, hipStream_t st) {
-  const dim3 grid((unsigned)((s.nH + 1) * (s.nH + 1) * (s.nH + 1) * bt.count));
-  if (mode == 0)
-    hipLaunchKernelGGL((k_small_patch<T, 0>), grid, dim3(256), 0, st, g, z, zc, s, gc, bt);
-  else if (mode == 1)
-    hipLaunchKernelGGL((k_small_patch<T, 1>), grid, dim3(256), 0, st, g, z, zc, s, gc, bt);
+  const int nv = s.nH + 1;
+  const bool two = small_pairs(s.nH, bt.count);
+  const dim3 grid((unsigned)((two ? nv / 2 + 1 : nv) * nv * nv * bt.count));
+  auto launch = [&](auto coef, auto pairs) {
+    constexpr bool C = decltype(coef)::value;
+    constexpr int NV = decltype(pairs)::value ? 2 : 1;
+    if (mode == 0)
+      hipLaunchKernelGGL((k_small_patch<T, 0, C, NV>), grid, dim3(256), 0, st, g, z, zc, s, gc, bt);
+    else if (mode == 1)
+      hipLaunchKernelGGL((k_small_patch<T, 1, C, NV>), grid, dim3(256), 0, st, g, z, zc, s, gc, bt);
+    else
+      hipLaunchKernelGGL((k_small_patch<T, 2, C, NV>), grid, dim3(256), 0, st, g, z, zc, s, gc, bt);
+  };
+  auto with_coef = [&](auto pairs) {
+    if (bt.coef)
+      launch(std::true_type{}, pairs);
+    else
+      launch(std::false_type{}, pairs);
+  };
+  if (two)
+    with_coef(std::true_type{});
   else
-    hipLaunchKernelGGL((k_small_patch<T, 2>), grid, dim3(256), 0, st, g, z, zc, s, gc, bt);
+    with_coef(std::false_type{});
   return hipGetLastError();
 }
 
@@ -481,8 +633,12 @@ hipError_t launch_small_pull(const T* r, T* z, const T* zc, int assign, const Sm
 template <typename T>
 hipError_t launch_small_restrict(const T* g, const T* z, T* out, const DGeom& f, double h, const DGeom& c,
                                  const Bat& bt, hipStream_t st) {
-  hipLaunchKernelGGL((k_small_restrict<T>), dim3((unsigned)(c.n * c.n * c.n * bt.count)), dim3(192), 0, st, g, z, out,
-                     f, h, c, bt);
+  const dim3 grid((unsigned)(c.n * c.n * c.n * bt.count));
+  const BoxDiv dv = bt.coef ? BoxDiv(c.n / bt.coef_r) : BoxDiv();
+  if (bt.coef)
+    hipLaunchKernelGGL((k_small_restrict<T, true>), grid, dim3(64), 0, st, g, z, out, f, h, c, dv, bt);
+  else
+    hipLaunchKernelGGL((k_small_restrict<T, false>), grid, dim3(64), 0, st, g, z, out, f, h, c, dv, bt);
   return hipGetLastError();
 }
 

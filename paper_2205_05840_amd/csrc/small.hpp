@@ -8,8 +8,17 @@
 
 namespace ndmg {
 
+// Box of a subdomain along an axis, u / w by a multiplication (exact for u w < 2^16).
+struct BoxDiv {
+  int w = 1, m = 65536;
+  BoxDiv() = default;
+  explicit BoxDiv(int w_) : w(w_), m((65536 + w_ - 1) / w_) {}
+  __host__ __device__ int box(int u) const { return (u * m) >> 16; }
+};
+
 // One smoothed level as the small-level kernels take it.  Factors of problem p follow each
-// other (36, 288 and sstride elements per problem).  Y: the patch results by vertex,
+// other (36, 288 and sstride elements per problem); with coefficient boxes (one problem)
+// A_T^{-1} and X_T hold a block per box, zero outside the domain.  Y: the patch results by vertex,
 // [(nH+1)^3][64] per pair.
 template <typename T>
 struct SmallSub {
@@ -17,6 +26,7 @@ struct SmallSub {
   double h;
   int nH;
   const uint32_t* tab;  // small_tables()
+  const int* cls;       // class triples of the vertices (BoxPatches), with coefficient boxes
   const T* ATinv;
   const T* XT;
   const T* Sinv;
@@ -24,14 +34,16 @@ struct SmallSub {
   T* Y;
   T* r;                 // interior residuals of the subdomains (modes with a residual)
   double eta;
+  BoxDiv dv;            // with coefficient boxes
 };
 
 // Packed tables of the 2 x 2 x 2 subdomain, built from the host's slot rules, five words per
 // entry.  kSmallEdges: the 48 boundary edges of a subdomain, then its 6 interior unknowns:
 // direction | offsets << 2, 4, 6 | 1 << 8 where the subdomain writes the unknown, then the
 // patch results it sums (corner | slot << 3, 0xffff none).  kSmallSlots: the 60 slots of a
-// vertex patch: position in the patch's cube ([direction][z][y][x], 5 nodes per axis), then the subdomains
-// of the patch whose boundary holds the edge (subdomain | boundary edge << 3).
+// vertex patch: direction | node in the patch's cube << 2, 5, 8 (x, y, z; the vertex at 2, 2,
+// 2), then the subdomains of the patch whose boundary holds the edge (subdomain | boundary
+// edge << 3).
 constexpr int kSmallEdges = 0, kSmallSlots = 5 * 54, kSmallWords = 5 * 114;
 const std::vector<uint32_t>& small_tables();   // built once
 
