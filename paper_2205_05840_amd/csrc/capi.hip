@@ -734,7 +734,6 @@ ndmg::GenLevel<T> gen_level(ndmg_ctx* c, const LevelHost& L) {
   Cd.ksplit = tb.npadI;
   Cd.npadK = tb.npadI;
   Cd.npadR = tb.npadB;
-  Cd.nrb = (tb.npadB + 63) / 64;
   Cd.ylen = L.clenG;
   Cd.nunits = (int64_t)tb.unitsI.size();
   auto& Ex = G.ext;    // z_I = eta [A_T^{-1} | -X_T] [r_I ; w_dT]
@@ -749,7 +748,6 @@ ndmg::GenLevel<T> gen_level(ndmg_ctx* c, const LevelHost& L) {
   Ex.ksplit = tb.nI;
   Ex.npadK = tb.npadE;
   Ex.npadR = tb.npadI;
-  Ex.nrb = (tb.npadI + 63) / 64;
   Ex.ylen = 0;
   auto& P = G.patch;   // y_P = S_P^{-1} g|Gamma_P
   common(P);
@@ -763,7 +761,6 @@ ndmg::GenLevel<T> gen_level(ndmg_ctx* c, const LevelHost& L) {
   P.ksplit = tb.npadP;
   P.npadK = tb.npadP;
   P.npadR = tb.npadP;
-  P.nrb = (tb.npadP + 63) / 64;
   P.ylen = L.ylenG;
   P.nunits = (int64_t)tb.unitsP.size();
   G.C = at<T>(c, L.o_C);
@@ -1021,7 +1018,8 @@ int vcycle_rec(ndmg_ctx* c, Cls& C, int k, const T* g, T* z, const ndmg::Bat& bt
   const T* none = nullptr;
   T* zc = at<T>(c, Lc.o_z);
   // (the launches of a batch's other size classes share the device with this one's)
-  if (!L.gen && ndmg::small_level(L.sub.nH, std::max(bt.count, pl.npairs))) {
+  const bool small = ndmg::small_level(L.g.n / 2, std::max(bt.count, pl.npairs));
+  if (!L.gen && small) {
     // the same steps, with the residual, the condensation, the prolongation and the patch
     // products in one launch, and the residual in the restriction's
     const ndmg::SmallSub<T> S = small_sub<T>(c, C, L);
@@ -1045,8 +1043,12 @@ int vcycle_rec(ndmg_ctx* c, Cls& C, int k, const T* g, T* z, const ndmg::Bat& bt
     NDMG_TRY(smooth_level<T>(c, C, L, P.r, z, bt, 0, st));
   }
   // gbar = I_k^{k-1} (g - A z_m)
-  NDMG_HIP(ndmg::launch_apply<T>(z, g, P.r, L.g, bt, 1, st));
-  NDMG_HIP(ndmg::launch_restrict<T>(P.r, at<T>(c, Lc.o_g), L.g, Lc.g, bt, st));
+  if (small) {
+    NDMG_HIP(ndmg::launch_small_restrict<T>(g, z, at<T>(c, Lc.o_g), ndmg::dgeom(L.g), L.g.h, ndmg::dgeom(Lc.g), bt, st));
+  } else {
+    NDMG_HIP(ndmg::launch_apply<T>(z, g, P.r, L.g, bt, 1, st));
+    NDMG_HIP(ndmg::launch_restrict<T>(P.r, at<T>(c, Lc.o_g), L.g, Lc.g, bt, st));
+  }
   NDMG_TRY(vcycle_rec<T>(c, C, k - 1, at<T>(c, Lc.o_g), zc, bt, st));
   // z_{m+1} = z_m + I_{k-1}^k MG(k-1, gbar, 0, m)
   NDMG_HIP(ndmg::launch_prolong_add<T>(zc, z, L.g, Lc.g, bt, st));
