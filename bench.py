@@ -97,7 +97,7 @@ def run_leg(torch, Solver, f, alpha, precision, steps, warmup):
 
 def time_apply(torch, S, reps=40, nbuf=8):
     """Average duration of the operator-apply kernel (one launch per ndmg_apply), timed
-    with HIP events on the library's stream, rotating over nbuf input/output pairs so that
+    with HIP events on the calls' stream, rotating over nbuf input/output pairs so that
     the 256 MB last-level cache cannot hold them.  The loop calls the C ABI directly (a
     few microseconds per call) so that the launches queue up ahead of the GPU and the
     events measure the kernels, not the host."""
@@ -111,7 +111,7 @@ def time_apply(torch, S, reps=40, nbuf=8):
     ptrs = [(xs[i].data_ptr(), ys[i].data_ptr()) for i in range(nbuf)]
     L = _lib.lib()
     torch.cuda.synchronize()
-    st = S.stream
+    st = torch.cuda.current_stream(S.device)   # the stream of the calls above
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     # a first batch of launches keeps the GPU busy while the timed ones are queued
     for i in range(nbuf):
@@ -138,7 +138,7 @@ def patch_flops(n):
 
 def time_patch(torch, S, reps=40):
     """Average duration of the fine-level patch products (k_sm_patch alone, one launch per
-    call), timed with HIP events on the library's stream over `reps` launches queued
+    call), timed with HIP events on the calls' stream over `reps` launches queued
     behind a first batch, on the condensed residual left by one smoother application."""
     from paper_2205_05840_amd import _lib
     r = (torch.randn(S.vec_len, dtype=torch.float64, device=S.device) * S.unknown_mask()).contiguous()
@@ -146,7 +146,7 @@ def time_patch(torch, S, reps=40):
     L = _lib.lib()
     ptr = r.data_ptr()
     torch.cuda.synchronize()
-    st = S.stream
+    st = torch.cuda.current_stream(S.device)   # the stream of the calls above
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     for _ in range(8):
         _lib.check(L.ndmg_level_op(S.ctx, -1, _lib.NDMG_OP_PATCH, ptr, ptr))

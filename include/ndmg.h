@@ -162,6 +162,11 @@ typedef struct ndmg_ctx ndmg_ctx;
 int ndmg_setup(ndmg_ctx** out, int nx, int ny, int nz, const double box[3], double alpha, int levels,
                const ndmg_opts* opts, void* d_workspace, size_t workspace_bytes, void* stream);
 
+/* ndmg_set_stream: later calls on the context enqueue on `stream` (a hipStream_t of the same
+ * device; NULL = default stream) instead of the one given at setup.  The caller orders it
+ * after the context's earlier work, whose level buffers it shares.  Errors: NDMG_EINVAL. */
+int ndmg_set_stream(ndmg_ctx* ctx, void* stream);
+
 /* ndmg_layout: describe the padded edge layout of a level (level 0 = coarsest,
  * level -1 = finest) of a context with a single problem size.  info[0] = n,
  * info[1] = P (row pitch), info[2] = B (block length), info[3] = vector length 3 B,
@@ -209,7 +214,8 @@ int ndmg_pcg_solve_batched(ndmg_ctx* ctx, const double* d_b, double* d_u, double
 /* ---- operations (all FP64 vectors in the padded layout of the finest level) -------- */
 
 /* y = A x with A the matrix of a(., .) on N_h (eq. def bilinear form, eq. fem):
- * y = alpha K x + M x.  d_x and d_y must not overlap.  Errors: NDMG_EINVAL, NDMG_EHIP. */
+ * y = alpha K x + M x.  d_x and d_y must not overlap.  Every entry of d_y is written (0 at
+ * the non-unknowns).  Errors: NDMG_EINVAL, NDMG_EHIP. */
 int ndmg_apply(ndmg_ctx* ctx, const double* d_x, double* d_y);
 
 /* z = MG(J, g, 0, m): one symmetric V-cycle (Fig. 1) with the vertex-based smoother of

@@ -24,7 +24,7 @@ EXPORTED = [
     "ndmg_plan_batched", "ndmg_setup_batched", "ndmg_batch_layout", "ndmg_pcg_solve_batched",
     "ndmg_curlcurl_form_noalloc", "ndmg_contraction", "ndmg_pcg_solve_warm", "ndmg_maxwell_step",
     "ndmg_source_key", "ndmg_tuning_load", "ndmg_tuning_set", "ndmg_tuning_clear", "ndmg_time_stencil",
-    "ndmg_stencil_shape",
+    "ndmg_stencil_shape", "ndmg_set_stream",
 ]
 
 # The autotuner's table of launch shapes (written by tune.py on the device); loaded with the
@@ -93,6 +93,7 @@ def lib():
     L.ndmg_batch_layout.argtypes = [vp, i, P(ctypes.c_int64)]
     L.ndmg_pcg_solve_batched.argtypes = [vp, vp, vp, d, i, P(i), P(d)]
     L.ndmg_destroy.argtypes = [vp]
+    L.ndmg_set_stream.argtypes = [vp, vp]
     L.ndmg_last_error.argtypes = []
     L.ndmg_last_error.restype = ctypes.c_char_p
     L.ndmg_source_key.argtypes = []
@@ -251,6 +252,10 @@ def ndmg_export_factor(ctx, level, which, typ=13):
 
 def ndmg_level_op(ctx, level, op, d_in, d_out):
     return check(lib().ndmg_level_op(ctx, level, op, d_in, d_out))
+
+
+def ndmg_set_stream(ctx, stream):
+    return check(lib().ndmg_set_stream(ctx, stream))
 
 
 def ndmg_destroy(ctx):

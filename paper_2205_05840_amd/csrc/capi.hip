@@ -1612,6 +1612,12 @@ int ndmg_setup_batched(ndmg_ctx** out, int nprob, const int* n, double length, c
   return setup_common(out, nprob, n, length, alpha, nrhs, opts, d_workspace, workspace_bytes, stream);
 }
 
+int ndmg_set_stream(ndmg_ctx* c, void* stream) {
+  if (int rc = check_ctx(c)) return rc;
+  c->st = static_cast<hipStream_t>(stream);
+  return NDMG_OK;
+}
+
 int ndmg_batch_layout(const ndmg_ctx* c, int prob, int64_t info[6]) {
   if (int rc = check_ctx(c)) return rc;
   if (!info) return fail(NDMG_EINVAL, "null info");
@@ -1653,7 +1659,7 @@ int ndmg_apply(ndmg_ctx* c, const double* x, double* y) {
   return for_classes(c, [&](size_t ci, hipStream_t st) {
     Cls& C = c->plan.cls[ci];
     NDMG_HIP(ndmg::launch_apply<double>(x + C.vec_off, nullptr, y + C.vec_off, C.lv.back().g,
-                                        class_batch(c, C, false), 0, st));
+                                        class_batch(c, C, false), 0, st, true));
     return NDMG_OK;
   });
 }

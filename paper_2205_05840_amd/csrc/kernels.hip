@@ -254,9 +254,20 @@ __device__ __forceinline__ void apply_node_coef(const T* __restrict__ x, const T
   }
 }
 
+// the padding of a row (positions n + 1 .. P - 1 of the three directions), by the lane at i = n
+template <typename T>
+__device__ __forceinline__ void zero_padding(T* __restrict__ y, const DGeom& g, int i, int j, int k) {
+  if (i != g.n) return;
+  for (int d = 0; d < 3; ++d)
+    for (int t = g.n + 1; t < g.P; ++t) y[d * g.B + lin(g, t, j, k)] = T(0);
+}
+
+// pad: also zero the padding, so that every entry of y is written (the level vectors inside
+// the V-cycle keep their zeros there)
 template <typename T, int MODE>
 __global__ void __launch_bounds__(64) k_apply(const T* __restrict__ x, const T* __restrict__ b,
-                                              T* __restrict__ y, DGeom g, Bat bt, double h, int nbx) {
+                                              T* __restrict__ y, DGeom g, Bat bt, double h, int nbx,
+                                              int pad) {
   const int3 bk = xcd_grid_block();
   const int pair = bk.x / nbx;
   const int i = (bk.x % nbx) * blockDim.x + threadIdx.x;
@@ -267,6 +278,7 @@ __global__ void __launch_bounds__(64) k_apply(const T* __restrict__ x, const T* 
   y += off;
   if (MODE == 1) b += off;
   const T ah = (T)(bt.alpha[pair / bt.nrhs] * h), h3 = (T)(h * h * h);
+  if (pad) zero_padding(y, g, i, j, k);
   if (bt.coef)
     apply_node_coef<T, MODE>(x, b, y, g, ah, h3, bt.coef, bt.coef_r, i, j, k);
   else
@@ -279,7 +291,8 @@ __global__ void __launch_bounds__(64) k_apply(const T* __restrict__ x, const T* 
 // blockIdx.y = k.
 template <typename T, int MODE>
 __global__ void __launch_bounds__(64) k_apply_plane(const T* __restrict__ x, const T* __restrict__ b,
-                                                    T* __restrict__ y, DGeom g, Bat bt, double h, int nbp) {
+                                                    T* __restrict__ y, DGeom g, Bat bt, double h, int nbp,
+                                                    int pad) {
   const int pair = blockIdx.x / nbp;
   const int t = (blockIdx.x % nbp) * blockDim.x + threadIdx.x;
   const int w = g.n + 1;
@@ -290,6 +303,7 @@ __global__ void __launch_bounds__(64) k_apply_plane(const T* __restrict__ x, con
   y += off;
   if (MODE == 1) b += off;
   const T ah = (T)(bt.alpha[pair / bt.nrhs] * h), h3 = (T)(h * h * h);
+  if (pad) zero_padding(y, g, i, j, k);
   if (bt.coef)
     apply_node_coef<T, MODE>(x, b, y, g, ah, h3, bt.coef, bt.coef_r, i, j, k);
   else
@@ -2153,7 +2167,7 @@ inline unsigned vec_blocks(int64_t len, int count, unsigned cap) {
 // ---------------------------------------------------------------------------------
 template <typename T>
 hipError_t launch_apply(const T* x, const T* b, T* y, const Geom& g, const Bat& bt, int mode,
-                        hipStream_t st) {
+                        hipStream_t st, bool pad) {
   // batches of four or more pairs take the plane-marching kernel from n = 17 in both
   // precisions (one position per lane up to n = 64: for the 512-problem batch FP32 165.6
   // against 182.7 ms per 2048 solves with the per-thread kernel at n = 24, 32)
@@ -2169,18 +2183,20 @@ hipError_t launch_apply(const T* x, const T* b, T* y, const Geom& g, const Bat& 
     const int w = g.n + 1, nbp = (w * w + 63) / 64;
     const dim3 grid((unsigned)(nbp * bt.count), (unsigned)w);
     if (mode == 0)
-      hipLaunchKernelGGL((k_apply_plane<T, 0>), grid, dim3(64), 0, st, x, b, y, dgeom(g), bt, g.h, nbp);
+      hipLaunchKernelGGL((k_apply_plane<T, 0>), grid, dim3(64), 0, st, x, b, y, dgeom(g), bt, g.h, nbp,
+                         pad ? 1 : 0);
     else
-      hipLaunchKernelGGL((k_apply_plane<T, 1>), grid, dim3(64), 0, st, x, b, y, dgeom(g), bt, g.h, nbp);
+      hipLaunchKernelGGL((k_apply_plane<T, 1>), grid, dim3(64), 0, st, x, b, y, dgeom(g), bt, g.h, nbp,
+                         pad ? 1 : 0);
     return hipGetLastError();
   }
   const int nbx = nbx64(g.n);
   if (mode == 0)
     hipLaunchKernelGGL((k_apply<T, 0>), node_grid(g, nbx, bt.count), dim3(64), 0, st, x, b, y, dgeom(g),
-                       bt, g.h, nbx);
+                       bt, g.h, nbx, pad ? 1 : 0);
   else
     hipLaunchKernelGGL((k_apply<T, 1>), node_grid(g, nbx, bt.count), dim3(64), 0, st, x, b, y, dgeom(g),
-                       bt, g.h, nbx);
+                       bt, g.h, nbx, pad ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -2486,7 +2502,7 @@ bool boundary_patches_match(const std::vector<int>& tab) {
 // explicit instantiations
 #define NDMG_INST(T)                                                                              \
   template hipError_t launch_apply<T>(const T*, const T*, T*, const Geom&, const Bat&, int,       \
-                                      hipStream_t);                                               \
+                                      hipStream_t, bool);                                               \
   template hipError_t launch_restrict<T>(const T*, T*, const Geom&, const Geom&, const Bat&,      \
                                          hipStream_t);                                            \
   template hipError_t launch_prolong_add<T>(const T*, T*, const Geom&, const Geom&, const Bat&,   \

@@ -156,10 +156,11 @@ template <typename T>
 hipError_t launch_stencil(const T* x, const T* b, T* y, const Geom& g, const Bat& bt, int mode,
                           double* part, int64_t pstride, double* dot, hipStream_t st);
 
-// y = A x (mode 0) or y = b - A x (mode 1); all entries of y in [0, n]^3 written.
+// y = A x (mode 0) or y = b - A x (mode 1); all entries of y in [0, n]^3 written, with pad
+// the row padding too (zeros).
 template <typename T>
 hipError_t launch_apply(const T* x, const T* b, T* y, const Geom& g, const Bat& bt, int mode,
-                        hipStream_t st);
+                        hipStream_t st, bool pad = false);
 
 // gc = I_k^{k-1} rf (restriction, eq. F2C); all entries of gc written.
 template <typename T>

@@ -437,6 +437,10 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
       // a lane stores its R positions when they lie inside the row (positions > n of the
       // row are padding and receive zero)
       const bool lane_in_row = i0 + R <= g.P;
+      // the positions n .. P - 1 of a row fall outside the lanes when n = 64 R (P = n + 8):
+      // the first P - n lanes write a zero each, so that every entry of y is written
+      const bool tail = g.n == 64 * R && lane < g.P - g.n;
+      const int toff = g.n + lane - i0;
       if (out_row && zero_row && ko >= k0 && ko < kend) {
         const int64_t rowoff = (int64_t)ko * g.plane + (int64_t)j * g.P + i0;
         const V zv = V(T(0));
@@ -444,9 +448,9 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
 #pragma unroll
           for (int d = 0; d < 3; ++d) *reinterpret_cast<V*>(y + d * g.B + rowoff) = zv;
         }
-        if (lane == 63 && i0 + R == g.n) {
+        if (tail) {
 #pragma unroll
-          for (int d = 0; d < 3; ++d) y[d * g.B + rowoff + R] = T(0);
+          for (int d = 0; d < 3; ++d) y[d * g.B + rowoff + toff] = T(0);
         }
       } else if (out_row && ko >= k0 && ko < kend) {
         T gzl[R], gyl[R];
@@ -505,10 +509,9 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
           *reinterpret_cast<V*>(y + g.B + rowoff) = oyv;
           *reinterpret_cast<V*>(y + 2 * g.B + rowoff) = ozv;
         }
-        // the position i = n of a row falls outside the lanes when n = 64 R: zero it
-        if (lane == 63 && i0 + R == g.n) {
+        if (tail) {
 #pragma unroll
-          for (int d = 0; d < 3; ++d) y[d * g.B + rowoff + R] = T(0);
+          for (int d = 0; d < 3; ++d) y[d * g.B + rowoff + toff] = T(0);
         }
       }
       // rotate the plane window

@@ -61,23 +61,49 @@ class _Context:
         self.ws_bytes = ws_bytes
         self.ws = torch.empty(ws_bytes + 256, dtype=torch.uint8, device=self.device)
         self._ws_ptr = (self.ws.data_ptr() + 255) // 256 * 256
-        # the library works on a stream of its own (default priority; graph capture needs a
-        # non-null stream); calls are ordered after the caller's current stream and the
-        # caller's stream waits for them
+        # solves run on a stream of the context's own (default priority; graph capture needs a
+        # non-null stream), ordered after the caller's current stream, which waits for them;
+        # single steps (apply, vcycle, ...) go straight to the caller's current stream
         self.stream = torch.cuda.Stream(device=self.device)
         self.stream.wait_stream(torch.cuda.current_stream(self.device))
+        self._last = self._bound = self.stream   # stream of the latest work; the library's stream
 
-    def _run(self, fn, *args):
+    def _bind(self, stream):
+        """Calls that follow enqueue on `stream`, after the context's earlier work."""
+        if self._last != stream and not torch.cuda.is_current_stream_capturing():
+            stream.wait_stream(self._last)
+        if self._bound != stream:
+            _lib.ndmg_set_stream(self.ctx, stream.cuda_stream)
+            self._bound = stream
+        self._last = stream
+
+    def _run(self, fn, *args, waits=False):
+        """A call on the context's own stream; waits: the call returns with its work done."""
         cur = torch.cuda.current_stream(self.device)
         self.stream.wait_stream(cur)
+        self._bind(self.stream)
+        done = False
         try:
-            return fn(self.ctx, *args)
+            res = fn(self.ctx, *args)
+            done = waits
+            return res
         finally:
-            cur.wait_stream(self.stream)
+            if not done:
+                cur.wait_stream(self.stream)
+
+    def _step(self, fn, *args):
+        """A call on the caller's current stream.  While that is being captured into a graph
+        the context's own stream joins the capture instead: work enqueued on other streams
+        before cannot be waited for there."""
+        if torch.cuda.is_current_stream_capturing():
+            return self._run(fn, *args)
+        self._bind(torch.cuda.current_stream(self.device))
+        return fn(self.ctx, *args)
 
     def close(self):
         if getattr(self, "ctx", None) is not None:
             self.stream.synchronize()
+            self._last.synchronize()
             _lib.ndmg_destroy(self.ctx)
             self.ctx = None
 
@@ -146,6 +172,10 @@ class Solver(_Context):
             lead = (self.nrhs,)
         return torch.zeros(*lead, self.vec_len, dtype=torch.float64, device=self.device)
 
+    def _empty(self):
+        shape = (self.nrhs, self.vec_len) if self.nrhs > 1 else (self.vec_len,)
+        return torch.empty(shape, dtype=torch.float64, device=self.device)
+
     def _check(self, t):
         if t.dtype != torch.float64 or t.device != self.device or not t.is_contiguous():
             raise ValueError("vectors must be contiguous float64 tensors on the solver's device")
@@ -190,30 +220,32 @@ class Solver(_Context):
     # ---- operations -----------------------------------------------------------------
 
     def apply(self, x, y=None):
-        y = self.zeros() if y is None else y
-        self._run(_lib.ndmg_apply, self._check(x), self._check(y))
+        y = self._empty() if y is None else y   # every entry is written
+        self._step(_lib.ndmg_apply, self._check(x), self._check(y))
         return y
 
     def vcycle(self, g, z=None):
-        z = self.zeros() if z is None else z
-        self._run(_lib.ndmg_vcycle, self._check(g), self._check(z))
+        # FP32: the whole result is converted into z; FP64: only unknowns are written
+        z = (self._empty() if self.precision == "fp32" else self.zeros()) if z is None else z
+        self._step(_lib.ndmg_vcycle, self._check(g), self._check(z))
         return z
 
     def solve(self, b, rtol=1e-10, maxit=500, u=None, raise_on_noconv=True, warm=False):
         """u = A^{-1} b by V-cycle PCG; returns (u, iterations, relative residual), the
         last two as lists over the right-hand sides when nrhs > 1.  warm: start from the
         values in u instead of 0."""
-        u = self.zeros() if u is None else u
+        if u is None:
+            u = self.zeros() if warm else self._empty()   # (the solve clears it)
         if warm:
             code, it, rel = self._run(_lib.ndmg_pcg_solve_warm, self._check(b), self._check(u), rtol, maxit,
-                                      self.nrhs, raise_on_noconv)
+                                      self.nrhs, raise_on_noconv, waits=True)
             return (u, it[0], rel[0]) if self.nrhs == 1 else (u, it, rel)
         if self.nrhs == 1:
             code, it, rel = self._run(_lib.ndmg_pcg_solve, self._check(b), self._check(u), rtol,
-                                      maxit, raise_on_noconv)
+                                      maxit, raise_on_noconv, waits=True)
             return u, it, rel
         code, it, rel = self._run(_lib.ndmg_pcg_solve_batched, self._check(b), self._check(u), rtol,
-                                  maxit, self.nrhs, raise_on_noconv)
+                                  maxit, self.nrhs, raise_on_noconv, waits=True)
         return u, it, rel
 
     def maxwell_step(self, f, u, v, a, dt, eps=1.0, sigma=0.0, mu=1.0, rtol=1e-10, maxit=500):
@@ -236,7 +268,7 @@ class Solver(_Context):
         if f.numel() != self.nrhs * self.n ** 3 * 24:
             raise ValueError("f must hold nrhs x n^3 x 8 x 3 values")
         b = self.zeros()
-        self._run(_lib.ndmg_assemble_rhs, f.data_ptr(), self._check(b))
+        self._step(_lib.ndmg_assemble_rhs, f.data_ptr(), self._check(b))
         return b
 
     def curlcurl_form(self, lam, u):
@@ -245,7 +277,7 @@ class Solver(_Context):
         u = u.reshape(-1, self.vec_len).contiguous()
         if lam.shape != u.shape or lam.dtype != torch.float64 or u.dtype != torch.float64:
             raise ValueError("lam and u must be float64 of the same shape")
-        return self._run(_lib.ndmg_curlcurl_form, lam.data_ptr(), u.data_ptr(), lam.shape[0])
+        return self._step(_lib.ndmg_curlcurl_form, lam.data_ptr(), u.data_ptr(), lam.shape[0])
 
     def level_op(self, level, op, x, out=None):
         """One step on one level (FP64 solvers): op in 'apply', 'smooth', 'restrict',
@@ -263,7 +295,7 @@ class Solver(_Context):
             out = torch.zeros(ln_out, dtype=torch.float64, device=self.device)
         if out.numel() != ln_out:
             raise ValueError("output has the wrong length")
-        self._run(_lib.ndmg_level_op, lvl, ops[op], x.data_ptr(), out.data_ptr())
+        self._step(_lib.ndmg_level_op, lvl, ops[op], x.data_ptr(), out.data_ptr())
         return out
 
     def export_factor(self, level, which, typ=13):
@@ -305,6 +337,9 @@ class BatchedSolver(_Context):
     def zeros(self):
         return torch.zeros(self.total_len, dtype=torch.float64, device=self.device)
 
+    def _empty(self):
+        return torch.empty(self.total_len, dtype=torch.float64, device=self.device)
+
     def view(self, X, p):
         """The [nrhs, vec_len] block of problem p in batch vector X (a view)."""
         off, vl = self.layouts[p][0], self.layouts[p][1]
@@ -324,13 +359,14 @@ class BatchedSolver(_Context):
         return t.data_ptr()
 
     def apply(self, x, y=None):
-        y = self.zeros() if y is None else y
-        self._run(_lib.ndmg_apply, self._check(x), self._check(y))
+        y = self._empty() if y is None else y   # every entry is written
+        self._step(_lib.ndmg_apply, self._check(x), self._check(y))
         return y
 
     def vcycle(self, g, z=None):
-        z = self.zeros() if z is None else z
-        self._run(_lib.ndmg_vcycle, self._check(g), self._check(z))
+        # FP32: the whole result is converted into z; FP64: only unknowns are written
+        z = (self._empty() if self.precision == "fp32" else self.zeros()) if z is None else z
+        self._step(_lib.ndmg_vcycle, self._check(g), self._check(z))
         return z
 
     def sample_len(self):
@@ -345,14 +381,14 @@ class BatchedSolver(_Context):
                 or f.numel() != self.sample_len()):
             raise ValueError(f"f must be a contiguous float64 tensor of {self.sample_len()} values")
         b = self.zeros()
-        self._run(_lib.ndmg_assemble_rhs, f.data_ptr(), self._check(b))
+        self._step(_lib.ndmg_assemble_rhs, f.data_ptr(), self._check(b))
         return b
 
     def solve(self, B, rtol=1e-10, maxit=500, U=None, raise_on_noconv=True):
         """U = A_p^{-1} B for every pair; returns (U, iterations [nprob, nrhs],
         relative residuals [nprob, nrhs])."""
-        U = self.zeros() if U is None else U
+        U = self._empty() if U is None else U   # (the solve clears it)
         code, it, rel = self._run(_lib.ndmg_pcg_solve_batched, self._check(B), self._check(U), rtol,
-                                  maxit, self.npairs, raise_on_noconv)
+                                  maxit, self.npairs, raise_on_noconv, waits=True)
         return (U, np.array(it, dtype=np.int64).reshape(self.nprob, self.nrhs),
                 np.array(rel).reshape(self.nprob, self.nrhs))

@@ -121,10 +121,10 @@ def _time_patch(torch, Solver, n, prec, reps=30):
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     for _ in range(5):
         _lib.check(L.ndmg_level_op(S.ctx, -1, _lib.NDMG_OP_PATCH, ptr, ptr))
-    e0.record(S.stream)
+    e0.record()
     for _ in range(reps):
         _lib.check(L.ndmg_level_op(S.ctx, -1, _lib.NDMG_OP_PATCH, ptr, ptr))
-    e1.record(S.stream)
+    e1.record()
     e1.synchronize()
     S.close()
     return e0.elapsed_time(e1) * 1e3 / reps
