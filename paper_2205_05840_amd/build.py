@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libndmg.so")
 
-SOURCES = ["kernels.hip", "stencil.hip", "generic.hip", "small.hip", "capi.hip", "host_setup.cpp", "tuning.cpp"]
+SOURCES = ["kernels.hip", "stencil.hip", "generic.hip", "small.hip", "cgstep.hip", "capi.hip", "host_setup.cpp", "tuning.cpp"]
 # the kernels whose launch shapes the autotuner measures: a tuning table is valid only for
 # the sources it was measured on
 TUNED_SOURCES = ["stencil.hip", "kernels.hip", "kernels.hpp", "reduce.hpp"]

@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "../../include/ndmg.h"
+#include "cgstep.hpp"
 #include "generic.hpp"
 #include "kernels.hpp"
 #include "small.hpp"
@@ -988,6 +989,17 @@ ndmg::SmallArgs<T> small_args(ndmg_ctx* c, Cls& C, int top) {
   return a;
 }
 
+// z = A_0^{-1} g on the coarsest level (no unknowns there, as in a thin box: nothing to do).
+template <typename T>
+int solve_coarse(ndmg_ctx* c, Cls& C, const T* g, T* z, const ndmg::Bat& bt, hipStream_t st) {
+  const LevelHost& L = C.lv[0];
+  if (L.map.empty()) return NDMG_OK;
+  // (A_0^{-1} is symmetric: the transposed form for many problems reads it as it is)
+  NDMG_HIP(ndmg::launch_dense_vcycle<T>(g, z, at<T>(c, L.o_A0), at<int64_t>(c, L.o_map), (int)L.map.size(), L.g.len, bt,
+                                        false, C.nprob >= 8, st));
+  return NDMG_OK;
+}
+
 // z = MG(k, g, 0, m) (Fig. 1) for the pairs of a class.
 template <typename T>
 int vcycle_rec(ndmg_ctx* c, Cls& C, int k, const T* g, T* z, const ndmg::Bat& bt, hipStream_t st) {
@@ -1001,15 +1013,13 @@ int vcycle_rec(ndmg_ctx* c, Cls& C, int k, const T* g, T* z, const ndmg::Bat& bt
     return NDMG_OK;
   }
   if (k == 0) {
-    NDMG_HIP(ndmg::launch_coarse<T>(g, z, at<T>(c, L.o_A0), at<int64_t>(c, L.o_map), (int)L.map.size(),
-                                    L.g.len, bt, st));
-    return NDMG_OK;
+    return solve_coarse<T>(c, C, g, z, bt, st);
   }
   if (k == C.dense_k) {
-    // z may be a caller's vector at the finest level: clear its non-unknown entries
-    const bool top = (k == (int)C.lv.size() - 1);
+    // a caller's vector: clear its non-unknown entries (the context's own hold zeros there)
+    const void* own = z == at<T>(c, L.o_z) ? (const void*)z : (const void*)at<double>(c, C.o_pz);
     NDMG_HIP(ndmg::launch_dense_vcycle<T>(g, z, at<T>(c, L.o_Bd), at<int64_t>(c, L.o_map), L.Nd, L.g.len, bt,
-                                          top, C.dense_t, st));
+                                          (const void*)z != own, C.dense_t, st));
     return NDMG_OK;
   }
   const int m = pl.opts.m;
@@ -1168,13 +1178,52 @@ bool flexible_beta(const Plan& pl) {
 
 // The convergence test of an iteration; its count of active pairs goes straight to host
 // set `set` (iterations alternate between the two sets).
-int pcg_check(ndmg_ctx* c, size_t ci, int i_rz, int set, hipStream_t st) {
+int pcg_check(ndmg_ctx* c, size_t ci, int i_rz, int set, int rr_n, hipStream_t st) {
   Cls& C = c->plan.cls[ci];
   NDMG_HIP(ndmg::launch_pcg_check(at<double>(c, C.o_scal), at<int>(c, C.o_act), at<int>(c, C.o_iters),
                                   at<int>(c, C.o_status), C.count, i_rz,
                                   c->dev_nact + set * c->plan.cls.size() + ci, part_region(c, C, 2),
-                                  ndmg::dot_parts(C.vlen, C.count), part_stride(C), at<double>(c, C.o_hist), st));
+                                  rr_n, part_stride(C), at<double>(c, C.o_hist), st));
   return NDMG_OK;
+}
+
+// Whether an iteration's vector work runs as one launch (launch_cg_step): while its block per
+// pair finds a compute unit of its own (with 2048 pairs in five classes the launches were 0.4 %
+// faster).
+bool one_step(const ndmg_ctx* c, const Cls& C) {
+  return C.n <= ndmg::kCgStepMaxN && c->plan.coef.empty() && c->plan.npairs <= 256;
+}
+
+// The vector work between two V-cycles and the convergence test as one launch (two with
+// several pairs); first: the start of a solve.
+int cg_step(ndmg_ctx* c, size_t ci, double* u, int cur, int nxt, bool first, int set, const ndmg::Bat& bt,
+            hipStream_t st) {
+  Cls& C = c->plan.cls[ci];
+  ndmg::CgStep s{};
+  s.r = at<double>(c, C.o_pr);
+  s.p = at<double>(c, C.o_pp);
+  s.q = at<double>(c, C.o_pq);
+  s.u = u;
+  s.r32 = r32_of(c, C);
+  s.scal = at<double>(c, C.o_scal);
+  s.act = at<int>(c, C.o_act);
+  s.iters = at<int>(c, C.o_iters);
+  s.status = at<int>(c, C.o_status);
+  s.hist = at<double>(c, C.o_hist);
+  s.nact = c->dev_nact + set * c->plan.cls.size() + ci;
+  s.rr_part = part_region(c, C, 2);
+  s.pstride = part_stride(C);
+  s.i_num = nxt;
+  s.i_den = s.i_an = cur;
+  s.i_zq = nxt + 1;
+  s.flexible = flexible_beta(c->plan);
+  s.first = first;
+  const ndmg::Geom& g = C.lv.back().g;
+  if (mixed(c->plan))
+    NDMG_HIP(ndmg::launch_cg_step<float>(at<float>(c, C.lv.back().o_z), s, g, bt, st));
+  else
+    NDMG_HIP(ndmg::launch_cg_step<double>(at<double>(c, C.o_pz), s, g, bt, st));
+  return C.count > 1 ? pcg_check(c, ci, nxt, set, 1, st) : NDMG_OK;
 }
 
 // Start of a solve for one class: r = b, u = 0, b . b, per-pair state, z = B r,
@@ -1200,6 +1249,7 @@ int pcg_prologue(ndmg_ctx* c, size_t ci, const double* b, double* u, double rtol
                                  C.count, rtol, st));
   if (mixed(c->plan)) NDMG_HIP((ndmg::launch_convert<double, float>(r, r32_of(c, C), len, act, st)));
   NDMG_TRY(precondition_cg(c, C, act, st));
+  if (one_step(c, C)) return cg_step(c, ci, u, kS_RZA, kS_RZA, true, 0, act, st);
   if (mixed(c->plan)) {
     const float* zf = at<float>(c, C.lv.back().o_z);
     NDMG_HIP(ndmg::launch_dot<float>(zf, r, nullptr, part, ps, sc + kS_RZA, len, act, st));
@@ -1209,7 +1259,7 @@ int pcg_prologue(ndmg_ctx* c, size_t ci, const double* b, double* u, double rtol
     NDMG_HIP(ndmg::launch_copy(z, p, len, act, st));
   }
   NDMG_TRY(cg_apply_update(c, C, kS_RZA, act, st));
-  return pcg_check(c, ci, kS_RZA, 0, st);
+  return pcg_check(c, ci, kS_RZA, 0, ndmg::dot_parts(len, C.count), st);
 }
 
 // One CG iteration after the first for one class: z = B r; s[nxt] = r . z (and
@@ -1229,6 +1279,8 @@ int pcg_body(ndmg_ctx* c, size_t ci, double* u, int cur, int nxt, hipStream_t st
   const bool flex = flexible_beta(c->plan);
   const ndmg::Bat act = class_batch(c, C, true);
   NDMG_TRY(precondition_cg(c, C, act, st));
+  const int set = cur == kS_RZA ? 1 : 0;
+  if (one_step(c, C)) return cg_step(c, ci, u, cur, nxt, false, set, act, st);
   // dot partials; the direction kernel reduces them (s[nxt] = r . z, s[nxt + 1] = z . q)
   if (mixed(c->plan)) {
     const float* zf = at<float>(c, C.lv.back().o_z);
@@ -1241,7 +1293,7 @@ int pcg_body(ndmg_ctx* c, size_t ci, double* u, int cur, int nxt, hipStream_t st
                                                nd, ps, len, act, st));
   }
   NDMG_TRY(cg_apply_update(c, C, nxt, act, st));
-  return pcg_check(c, ci, nxt, cur == kS_RZA ? 1 : 0, st);
+  return pcg_check(c, ci, nxt, set, ndmg::dot_parts(len, C.count), st);
 }
 
 // Run fn(ci, stream) for every class: class 0 on the context's stream, class i >= 1 on
@@ -1279,16 +1331,19 @@ void drop_graphs(ndmg_ctx* c) {
   c->graph_u = nullptr;
 }
 
-// Graphs for the CG iterations: as asked, or (use_graphs -1) unless one size class with a
-// finest level of n >= 80 makes each iteration long enough for eager launches to keep
-// ahead of the device.
-bool use_graphs(const Plan& pl) {
+// Graphs for the CG iterations: as asked, or (use_graphs -1) unless one size class makes eager
+// launches the faster ones: a finest level of n >= 64, whose iterations are long enough for
+// them to keep ahead of the device (64^3 FP64 5.40 against 5.56 ms per solve with graphs, FP32
+// equal, 48^3 4.17 against 3.93), or an iteration of a few launches (one_step: 8^3 0.50
+// against 0.63 to 0.73 ms, 12^3 1.22 against 1.27).
+bool use_graphs(const ndmg_ctx* c) {
+  const Plan& pl = c->plan;
   if (pl.opts.use_graphs >= 0) return pl.opts.use_graphs != 0;
-  return !(pl.cls.size() == 1 && pl.cls[0].lv.back().g.n >= 80);
+  return !(pl.cls.size() == 1 && (pl.cls[0].lv.back().g.n >= 64 || one_step(c, pl.cls[0])));
 }
 
 int body_all(ndmg_ctx* c, double* u, int cur, int nxt) {
-  if (!use_graphs(c->plan) || c->st == nullptr) return body_all_eager(c, u, cur, nxt);
+  if (!use_graphs(c) || c->st == nullptr) return body_all_eager(c, u, cur, nxt);
   if (c->graph_u != u) drop_graphs(c);
   const int par = (cur == kS_RZA) ? 0 : 1;
   if (!c->gexec[par]) {
@@ -2115,9 +2170,7 @@ int level_op_t(ndmg_ctx* c, Cls& C, int level, int op, const T* in, T* out, cons
       }
       return NDMG_OK;
     default:   // NDMG_OP_COARSE
-      NDMG_HIP(ndmg::launch_coarse<T>(in, out, at<T>(c, L.o_A0), at<int64_t>(c, L.o_map), (int)L.map.size(),
-                                      L.g.len, bt, c->st));
-      return NDMG_OK;
+      return solve_coarse<T>(c, C, in, out, bt, c->st);
   }
 }
 

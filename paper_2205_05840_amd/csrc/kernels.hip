@@ -868,29 +868,6 @@ __device__ __forceinline__ void extend_sub_s2(const T* __restrict__ w, const T* 
 }
 
 
-// ---------------------------------------------------------------------------------
-// coarsest level: dense inverse (one workgroup per pair)
-// ---------------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256) k_coarse(const T* __restrict__ g, T* __restrict__ z,
-                                                const T* __restrict__ A0inv,
-                                                const int64_t* __restrict__ map, int N0, int64_t len,
-                                                Bat bt) {
-  __shared__ T gl[1024];
-  const int pair = blockIdx.x;
-  if (inactive(bt, pair)) return;
-  g += (int64_t)pair * len;
-  z += (int64_t)pair * len;
-  A0inv += (int64_t)(pair / bt.nrhs) * N0 * N0;
-  for (int i = threadIdx.x; i < N0; i += blockDim.x) gl[i] = g[map[i]];
-  __syncthreads();
-  for (int i = threadIdx.x; i < N0; i += blockDim.x) {
-    T s = T(0);
-    for (int j = 0; j < N0; ++j) s += A0inv[(int64_t)i * N0 + j] * gl[j];
-    z[map[i]] = s;
-  }
-}
-
 // Patches holding each boundary edge of a 2 x 2 x 2 subdomain, computed at compile time
 // by the rules of the host tables (vertex_slots, boundary_dofs, boundary_patch_table),
 // which setup compares against them: the boundary edges in order (direction, then z, y,
@@ -1342,7 +1319,7 @@ __global__ void __launch_bounds__(256) k_dense_vcycle_t(const T* __restrict__ g,
   const T* __restrict__ Bp = Bt + (int64_t)prob * N * N;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int ic = i < N ? i : 0;
-  for (int rc = 0; rc < nr; rc += RC) {
+  for (int rc = blockIdx.z * RC; rc < nr; rc += gridDim.z * RC) {
     const int nrc = min(RC, nr - rc);
     bool live[RC];
 #pragma unroll
@@ -1421,7 +1398,7 @@ __global__ void __launch_bounds__(256) k_dense_vcycle(const T* __restrict__ g, T
       }
     }
   };
-  for (int rc = 0; rc < nr; rc += RC) {
+  for (int rc = blockIdx.z * RC; rc < nr; rc += gridDim.z * RC) {
     const int nrc = min(RC, nr - rc);
     bool live[RC];
 #pragma unroll
@@ -2288,15 +2265,6 @@ hipError_t launch_patch_products(const LevelPtrs<T>& L, const DSub& sub, const G
 }
 
 template <typename T>
-hipError_t launch_coarse(const T* g, T* z, const T* A0inv, const int64_t* map, int N0,
-                         int64_t len, const Bat& bt, hipStream_t st) {
-  if (N0 > 1024) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_coarse<T>), dim3((unsigned)bt.count), dim3(256), 0, st, g, z, A0inv, map, N0,
-                     len, bt);
-  return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_unit_cols(T* g, const int64_t* map, int N, int j0, int64_t len, const Bat& bt,
                             hipStream_t st) {
   hipLaunchKernelGGL((k_unit_cols<T>), dim3(vec_blocks(len, bt.count, 64), (unsigned)bt.count), dim3(256), 0, st,
@@ -2320,8 +2288,15 @@ hipError_t launch_dense_vcycle(const T* g, T* z, const T* Bm, const int64_t* map
     hipLaunchKernelGGL((k_fill_zero<T>), dim3(vec_blocks(len, bt.count, 2048), (unsigned)bt.count), dim3(256), 0,
                        st, z, len, bt);
   const int nprob = bt.count / bt.nrhs;
+  // right-hand sides in chunks of RC along z: as many at once as fill the chip twice (each
+  // reads the matrix again, from L2 or the last-level cache), the rest in turn
+  const int rc = bt.nrhs == 1 ? 1 : 4, nrc = (bt.nrhs + rc - 1) / rc;
+  auto chunks = [&](unsigned nbx) {
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(nrc, 1024 / ((int64_t)nbx * nprob)));
+  };
   if (colmajor) {
-    const dim3 grid((unsigned)((N + 255) / 256), (unsigned)nprob);
+    const unsigned nbx = (unsigned)((N + 255) / 256);
+    const dim3 grid(nbx, (unsigned)nprob, chunks(nbx));
     if (bt.nrhs == 1)
       hipLaunchKernelGGL((k_dense_vcycle_t<T, 1>), grid, dim3(256), (size_t)N * sizeof(T), st, g, z, Bm, map, N,
                          len, bt);
@@ -2334,12 +2309,13 @@ hipError_t launch_dense_vcycle(const T* g, T* z, const T* Bm, const int64_t* map
   const int64_t want = (int64_t)N * nprob / (4 * 1024);
   const int rpw = (int)std::max<int64_t>(1, std::min<int64_t>(16, want));
   const unsigned nbx = (unsigned)((N + 4 * rpw - 1) / (4 * rpw));
+  const dim3 grid(nbx, (unsigned)nprob, chunks(nbx));
   if (bt.nrhs == 1) {
-    hipLaunchKernelGGL((k_dense_vcycle<T, 1>), dim3(nbx, (unsigned)nprob), dim3(256), (size_t)N * sizeof(T), st, g,
-                       z, Bm, map, N, len, rpw, bt);
+    hipLaunchKernelGGL((k_dense_vcycle<T, 1>), grid, dim3(256), (size_t)N * sizeof(T), st, g, z, Bm, map, N, len, rpw,
+                       bt);
   } else {
-    hipLaunchKernelGGL((k_dense_vcycle<T, 4>), dim3(nbx, (unsigned)nprob), dim3(256), (size_t)4 * N * sizeof(T),
-                       st, g, z, Bm, map, N, len, rpw, bt);
+    hipLaunchKernelGGL((k_dense_vcycle<T, 4>), grid, dim3(256), (size_t)4 * N * sizeof(T), st, g, z, Bm, map, N, len,
+                       rpw, bt);
   }
   return hipGetLastError();
 }
@@ -2511,8 +2487,6 @@ bool boundary_patches_match(const std::vector<int>& tab) {
                                        const Geom&, const Bat&, double, int, hipStream_t);       \
   template hipError_t launch_patch_products<T>(const LevelPtrs<T>&, const DSub&, const Geom&,     \
                                                const Bat&, hipStream_t);                          \
-  template hipError_t launch_coarse<T>(const T*, T*, const T*, const int64_t*, int, int64_t,      \
-                                       const Bat&, hipStream_t);                                  \
   template hipError_t launch_unit_cols<T>(T*, const int64_t*, int, int, int64_t, const Bat&,      \
                                           hipStream_t);                                           \
   template hipError_t launch_gather_cols<T>(const T*, T*, const int64_t*, int, int, int64_t, bool, \

@@ -220,11 +220,6 @@ struct SmallArgs {
 template <typename T>
 hipError_t launch_vcycle_small(const SmallArgs<T>& a, const Bat& bt, hipStream_t st);
 
-// z = A_0^{-1} g on the coarsest level (A0inv: N0 x N0 per problem).
-template <typename T>
-hipError_t launch_coarse(const T* g, T* z, const T* A0inv, const int64_t* map, int N0,
-                         int64_t len, const Bat& bt, hipStream_t st);
-
 // The V-cycle from one level down as a dense matrix per problem (MG(k, g, 0, m) is linear
 // in g).  Build, per chunk of columns j0 .. j0 + K - 1 (K = bt.nrhs, pair = problem * K +
 // column - j0): g = unit vectors, then the recursive V-cycle, then the results become
@@ -236,7 +231,7 @@ hipError_t launch_unit_cols(T* g, const int64_t* map, int N, int j0, int64_t len
 template <typename T>
 hipError_t launch_gather_cols(const T* z, T* Bm, const int64_t* map, int N, int j0, int64_t len, bool colmajor,
                               const Bat& bt, hipStream_t st);
-// z = Bm g for every pair (Bm of problem pair / nrhs, stored transposed when colmajor:
+// z = Bm g for every pair (also the coarsest solve, with A_0^{-1}; Bm of problem pair / nrhs, stored transposed when colmajor:
 // one thread per row, for classes of many problems); clear: zero all of z first (for
 // output vectors whose non-unknown entries the caller may not have zeroed).
 template <typename T>
