@@ -2145,9 +2145,9 @@ inline unsigned vec_blocks(int64_t len, int count, unsigned cap) {
 template <typename T>
 hipError_t launch_apply(const T* x, const T* b, T* y, const Geom& g, const Bat& bt, int mode,
                         hipStream_t st, bool pad) {
-  // batches of four or more pairs take the plane-marching kernel from n = 17 in both
-  // precisions (one position per lane up to n = 64: for the 512-problem batch FP32 165.6
-  // against 182.7 ms per 2048 solves with the per-thread kernel at n = 24, 32)
+  // batches of four or more pairs take the plane-marching kernel from n = 17, of 64 or more
+  // from n = 9, in both precisions, several rows per wave (residual of 400 pairs, FP32:
+  // 16^3 33 against 52 us one thread per node, 12^3 20 against 25)
   const int min_n = stencil_min_n(bt.count);
   // with a coefficient per cell the plane-marching kernel takes box grids of up to 8^3
   // (its factors in LDS); others, and the smaller levels, take the per-thread kernels

@@ -16,6 +16,14 @@
 // Lane l owns positions i = R l + r, r < R, so one wave spans a row of up to 64 R
 // positions; neighbours along x come from the same lane or from lanes l -+ 1 through
 // DPP wave shifts (lanes outside the wave read zero, which is the boundary value).
+// Rows of at most 32 (16) positions leave half (three quarters) of such a wave idle, so there
+// a wave holds RW = 2 (4) consecutive rows, 64 / RW lanes each.  A shift then brings the last
+// lane of one row into the first of the next and the reverse: position 0 receives a value of
+// the row before, which only feeds the y- and z-edges at i = 0 (boundary: not written), and
+// the last position receives the z, y, F_x or T y at i = 0 of the next row, which are zero.
+// Bound by the memory rate once enough blocks share a compute unit: 400 pairs of 24^3, FP32
+// residual 114 -> 73 us, FP64 apply with p^T A p 206 -> 98 us (1.9 -> 3.9 TB/s); of 32^3 241
+// -> 150 and 309 -> 186 us (4.5 TB/s); of 16^3 52 (one thread per node) -> 33 us.
 // The workgroup marches k over its planes.  Step s emits the outputs of plane s - 1.
 //
 // Input planes stream through a ring of D plane slots in LDS, filled by direct
@@ -33,6 +41,7 @@
 // which are written as zero.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <cstdint>
 #include <type_traits>
@@ -169,7 +178,7 @@ struct Unroll<U, U> {
 // mode, the dot mode's p^T A p included, takes the per-cell form.
 constexpr int kCoefMaxR = 8;
 
-template <typename T, int R, int NW, int D, int MODE, int SYNC, bool COEF>
+template <typename T, int R, int RW, int NW, int D, int MODE, int SYNC, bool COEF>
 __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, const T* __restrict__ bv,
                                                      T* __restrict__ y, DGeom g, Bat bt, double h,
                                                      int KZ, int ntj, int ntiles,
@@ -177,7 +186,9 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
                                                      int opaque0) {
   constexpr int ROWS = (MODE == 1) ? 6 : 3;
   using RG = RingGeo<T, R, ROWS>;
-  constexpr int TJ = NW - 2;
+  constexpr int LW = 64 / RW;        // lanes per row
+  constexpr int NR = RW * NW;        // rows of the tile, two of them halo
+  constexpr int TJ = NR - 2;
   constexpr int CH = RG::CH, NQ = RG::NQ, VE = RG::VE;
   static_assert(D == 3 || D == 4, "ring depth 3 or 4");
   // steps are unrolled by U = D so that every ring slot index is static
@@ -205,7 +216,7 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
   static_assert(!COEF || D * NW * CH + (kOneBarrier ? 2 : 1) * 5 * NW * 64 * (int)sizeof(V) +
                                  kCoefN * (int)sizeof(T) + 1024 <= 160 * 1024,
                 "the box factors must fit the LDS beside the ring");
-  __shared__ V sBuf[kOneBarrier ? 2 : 1][5][NW][64];
+  __shared__ V sBuf[kOneBarrier ? 2 : 1][5][NW * 64];
   __shared__ T sCoef[kCoefN];
 
   const int pair = blockIdx.y;
@@ -237,16 +248,27 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
   // output planes [k0, kend); the last tile also writes the boundary plane k = n (zero)
   const int kend = (k0 + KZ >= g.n) ? g.n + 1 : k0 + KZ;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int j = j0 - 1 + wave;
-  const int i0 = R * lane;
-  // ring reads start at i0 + opaque0 (opaque0 = 0 from the host): an offset the compiler
+  const int sub = RW > 1 ? lane / LW : 0, pl = RW > 1 ? lane % LW : lane;
+  const int row = RW * wave + sub;   // row of the tile
+  const int j = j0 - 1 + row;
+  const int i0 = R * pl;
+  // ring reads start at R lane + opaque0 (opaque0 = 0 from the host): an offset the compiler
   // cannot bound makes every read of a slot overlap that slot's direct loads, so the waits
   // it adds for them are the ones for the slot's own (already completed) loads
-  const int ir = i0 + opaque0;
+  const int ir = R * lane + opaque0;
+  // ring position of the row above: in the wave's own chunk, or the first row of the next
+  // wave's (the tile's last row has none and reads itself)
+  const bool up_next = sub + 1 == RW && wave + 1 < NW;
+  const int up_off = (up_next ? (wave + 1) * CH : wave * CH);
+  const int up_ir = RW == 1 || (sub + 1 == RW && wave + 1 == NW) ? ir : up_next ? ir - (RW - 1) * LW * R : ir + LW * R;
+  // exchange slots of this lane and of the rows below and above (a halo row without one
+  // reads itself)
+  const int xo = wave * 64 + lane;
+  const int xl = row > 0 ? xo - LW : xo, xh = row + 1 < NR ? xo + LW : xo;
   // output rows: j0 .. j0 + TJ - 1, plus the boundary row j = n (all zero) when it is the
   // top halo row of the last tile (tiles cover rows 0 .. n - 1)
-  const bool zero_row = (wave == NW - 1 && j == g.n);
-  const bool out_row = active && j <= g.n && ((wave >= 1 && wave <= TJ) || zero_row);
+  const bool zero_row = (row == NR - 1 && j == g.n);
+  const bool out_row = active && j <= g.n && ((row >= 1 && row <= TJ) || zero_row);
   const bool row_ok = (j >= 0 && j < g.n);
   const T t6 = T(1) / T(6), t23 = T(2) / T(3), t3 = T(1) / T(3);
   // COEF: box of a cell index (clamped into the cube: a clamped cell only meets faces
@@ -264,11 +286,14 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
   // position) of the 16 bytes it copies in each of the NQ loads of a chunk; lanes past
   // the rows copy the vector's first bytes into the chunk's padding
   const T* src_base[NQ];
+  int src_row[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
     const int o = q * 1024 + 16 * lane;
     const int d = o / RG::RB;
-    const int p = min((o % RG::RB) / (int)sizeof(T), g.P - VE);
+    const int e = (o % RG::RB) / (int)sizeof(T);
+    const int p = min(RW > 1 ? e % (LW * R) : e, g.P - VE);
+    src_row[q] = j0 - 1 + RW * wave + (RW > 1 ? e / (LW * R) : 0);
     if (d < 3) src_base[q] = x + (int64_t)d * g.B + p;
     else if (MODE == 1 && d < 6) src_base[q] = bv + (int64_t)(d - 3) * g.B + p;
     else src_base[q] = x;
@@ -284,13 +309,24 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
   // loads of other planes (and of rows outside [0, n)) read row (0, 0) of plane 0, which
   // is zero and stays cached, so they cost no memory traffic
   auto issue_plane = [&](auto SL, int p) {
-    const bool ok = row_ok && p >= 0 && p < g.n && p >= k0 - 1 && p <= kend;
-    const int64_t roff = ok ? (int64_t)p * g.plane + (int64_t)j * g.P : 0;
+    const bool okp = p >= 0 && p < g.n && p >= k0 - 1 && p <= kend;
     unsigned char* dst = slot_base(SL) + wave * CH;
+    if constexpr (RW == 1) {   // (one row offset for all loads: 26.8 us at 128^3 in FP64, per load 31.3)
+      const bool ok = okp && row_ok;
+      const int64_t roff = ok ? (int64_t)p * g.plane + (int64_t)j * g.P : 0;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-      __builtin_amdgcn_global_load_lds((const void*)(src_base[q] + roff), (lds_ptr_t)(dst + q * 1024), 16,
-                                       0, 0);
+      for (int q = 0; q < NQ; ++q)
+        __builtin_amdgcn_global_load_lds((const void*)(src_base[q] + roff), (lds_ptr_t)(dst + q * 1024), 16,
+                                         0, 0);
+    } else {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const bool ok = okp && src_row[q] >= 0 && src_row[q] < g.n;
+        const int64_t roff = ok ? (int64_t)p * g.plane + (int64_t)src_row[q] * g.P : 0;
+        __builtin_amdgcn_global_load_lds((const void*)(src_base[q] + roff), (lds_ptr_t)(dst + q * 1024), 16,
+                                         0, 0);
+      }
+    }
   };
   // registers: x, y at planes s-2, s-1, s (index 0, 1, 2) and the new plane s+1 (3)
   T xp[4][R], yp[4][R], zp[2][R];   // z at s-1, s
@@ -321,7 +357,7 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
     constexpr int sl_next = (ph + 1) % D;       // plane s + 1
     T bcur[3][R];   // b of the output plane s - 1 (residual mode)
     // this step's copy of the exchange area
-    V(*sB)[NW][64] = sBuf[kOneBarrier ? (s & 1) : 0];
+    V(*sB)[NW * 64] = sBuf[kOneBarrier ? (s & 1) : 0];
     if constexpr (compute) {
       wait_vm_lds<NWAIT>();
       // plane s + 1 is in the ring; every wave is done with step s - 1.  With two copies
@@ -351,10 +387,9 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
       // halo row's outputs, which are not written)
       T xj[R], zj[R];
       {
-        const unsigned char* up =
-            slot_base(std::integral_constant<int, sl_cur>()) + (wave + 1 < NW ? wave + 1 : wave) * CH;
-        ring_row<T, R>(up, 0, ir, xj);
-        ring_row<T, R>(up, 2, ir, zj);
+        const unsigned char* up = slot_base(std::integral_constant<int, sl_cur>()) + up_off;
+        ring_row<T, R>(up, 0, up_ir, xj);
+        ring_row<T, R>(up, 2, up_ir, zj);
       }
       T zi1[R], yi1[R];
       shl1<T, R>(zp[1], zi1);
@@ -408,20 +443,19 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
           v3[r] = Tzx[r];
           v4[r] = Txz[r];
         }
-        sB[0][wave][lane] = v0;
-        sB[1][wave][lane] = v1;
-        sB[2][wave][lane] = v2;
-        sB[3][wave][lane] = v3;
-        sB[4][wave][lane] = v4;
+        sB[0][xo] = v0;
+        sB[1][xo] = v1;
+        sB[2][xo] = v2;
+        sB[3][xo] = v3;
+        sB[4][xo] = v4;
       }
       wait_lds();
       wg_barrier();
-      // rows j - 1 and j + 1 (the first and last wave have none: their values only feed
+      // rows j - 1 and j + 1 (the first and last row have none: their values only feed
       // the halo rows, whose outputs are not written)
-      const int wl = wave > 0 ? wave - 1 : wave, wh = wave + 1 < NW ? wave + 1 : wave;
       T Gy[R];
       {
-        const V fyl = sB[0][wl][lane], fyh = sB[0][wh][lane];
+        const V fyl = sB[0][xl], fyh = sB[0][xh];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           if constexpr (COEF) {
@@ -437,10 +471,10 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
       // a lane stores its R positions when they lie inside the row (positions > n of the
       // row are padding and receive zero)
       const bool lane_in_row = i0 + R <= g.P;
-      // the positions n .. P - 1 of a row fall outside the lanes when n = 64 R (P = n + 8):
-      // the first P - n lanes write a zero each, so that every entry of y is written
-      const bool tail = g.n == 64 * R && lane < g.P - g.n;
-      const int toff = g.n + lane - i0;
+      // the positions n .. P - 1 of a row fall outside the lanes when n = LW R (P = n + 8):
+      // its first P - n lanes write a zero each, so that every entry of y is written
+      const bool tail = g.n == LW * R && pl < g.P - g.n;
+      const int toff = g.n + pl - i0;
       if (out_row && zero_row && ko >= k0 && ko < kend) {
         const int64_t rowoff = (int64_t)ko * g.plane + (int64_t)j * g.P + i0;
         const V zv = V(T(0));
@@ -457,10 +491,10 @@ __global__ void __launch_bounds__(64 * NW) k_stencil(const T* __restrict__ x, co
         shr1<T, R>(Gz1, gzl);
         shr1<T, R>(gy[1], gyl);
         const int64_t rowoff = (int64_t)ko * g.plane + (int64_t)j * g.P + i0;
-        // wave > 0 and wave + 1 < NW here
-        const V gzjmv = sB[1][wave - 1][lane], gxjmv = sB[2][wave - 1][lane];
-        const V txl = sB[3][wave - 1][lane], txh = sB[3][wave + 1][lane];
-        const V tzl = sB[4][wave - 1][lane], tzh = sB[4][wave + 1][lane];
+        // row > 0 and row + 1 < NR here
+        const V gzjmv = sB[1][xo - LW], gxjmv = sB[2][xo - LW];
+        const V txl = sB[3][xo - LW], txh = sB[3][xo + LW];
+        const V tzl = sB[4][xo - LW], tzh = sB[4][xo + LW];
         V oxv, oyv, ozv;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -550,9 +584,9 @@ struct Tiling {
 
 // Tiles cover rows and planes 0 .. n - 1 (the boundary row and plane n ride along with
 // the last tiles).
-Tiling tiling(int n, int NW, int KZ) {
+Tiling tiling(int n, int rows, int KZ) {
   Tiling t;
-  const int TJ = NW - 2;
+  const int TJ = rows - 2;
   t.ntj = (n + TJ - 1) / TJ;
   t.KZ = KZ;
   const int ntk = (n + KZ - 1) / KZ;
@@ -561,20 +595,20 @@ Tiling tiling(int n, int NW, int KZ) {
   return t;
 }
 
-template <typename T, int R, int NW, int D, int MODE, int SYNC = 2>
+template <typename T, int R, int RW, int NW, int D, int MODE, int SYNC = 2>
 hipError_t launch_m(const T* x, const T* b, T* y, const Geom& g, const Bat& bt, int KZ, double* part,
                     int64_t pstride, double* dot, hipStream_t st) {
-  const Tiling tl = tiling(g.n, NW, KZ);
+  const Tiling tl = tiling(g.n, RW * NW, KZ);
   if (MODE == 2 && (part == nullptr || tl.ntiles > pstride)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)tl.nblocks, (unsigned)bt.count);
   if (bt.coef != nullptr) {
     if (bt.coef_r < 1 || bt.coef_r > kCoefMaxR || g.n % bt.coef_r) return hipErrorNotSupported;
-    hipLaunchKernelGGL((k_stencil<T, R, NW, D, MODE, SYNC, true>), grid, dim3(64 * NW), 0, st, x, b, y, dgeom(g),
+    hipLaunchKernelGGL((k_stencil<T, R, RW, NW, D, MODE, SYNC, true>), grid, dim3(64 * NW), 0, st, x, b, y, dgeom(g),
                        bt, g.h, tl.KZ, tl.ntj, tl.ntiles, part, pstride, 0);
     if (MODE == 2 && dot != nullptr) return launch_final(part, tl.ntiles, pstride, 1, dot, bt, st);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((k_stencil<T, R, NW, D, MODE, SYNC, false>), grid, dim3(64 * NW), 0, st, x, b, y, dgeom(g),
+  hipLaunchKernelGGL((k_stencil<T, R, RW, NW, D, MODE, SYNC, false>), grid, dim3(64 * NW), 0, st, x, b, y, dgeom(g),
                      bt, g.h, tl.KZ, tl.ntj, tl.ntiles, part, pstride, 0);
   if (MODE == 2 && dot != nullptr) return launch_final(part, tl.ntiles, pstride, 1, dot, bt, st);
   return hipGetLastError();
@@ -624,12 +658,41 @@ Choice choose_kz(int n, int count, Variant v) {
   return best;
 }
 
+// The shape for rows of 32 or 16 positions (several rows per wave; batches).  Blocks of two
+// to four waves share a compute unit (9 to 47 KB of LDS each), so their number, not whole
+// rounds, decides: the variant that computes fewest rows, halo rows and two more for a
+// block's start included, and the fewest parts along k, at least RW, that give 768 blocks
+// (24^3, FP32 residual of 400 pairs: 12 planes 73 us, 24 planes 111, 6 planes 78; of 64
+// pairs 8 planes 17.2, 24 planes 27; 16 pairs FP64 apply: 2 planes 10.2, 8 planes 12.7;
+// 16^3, FP32 residual of 400 pairs: 4 planes 33, 8 planes 45).
+template <int RW, typename VS>
+Choice choose_short(int n, int count, const VS& vs, int nv, int* which) {
+  int best = INT_MAX, ntj = 1;
+  for (int i = 0; i < nv; ++i) {
+    const int rows = RW * vs[i].nw, t = (n + rows - 3) / (rows - 2);
+    if (t * (rows + 2) < best) {
+      best = t * (rows + 2);
+      ntj = t;
+      *which = i;
+    }
+  }
+  const int64_t per = (int64_t)ntj * count;
+  const int ntk = (int)std::max<int64_t>(RW, std::min<int64_t>((768 + per - 1) / per, n / 2));
+  return Choice{(n + ntk - 1) / ntk, 0};
+}
+
 // Candidate variants per precision, row length and mode (index 0 or 1 of the
 // instantiated pair below); returns the chosen one and its KZ.
-template <typename T, int R>
+template <typename T, int R, int RW>
 void variants(int mode, Variant (&vs)[4], int* nv) {
   constexpr bool f64 = std::is_same<T, double>::value;
-  if (R == 1) {
+  if (RW == 4) {
+    // rows of 16 positions: 10 or 6 output rows
+    vs[0] = {3, 3, 2}; vs[1] = {2, 3, 2}; *nv = 2;
+  } else if (RW == 2) {
+    // rows of 32 positions: 6 or 4 output rows
+    vs[0] = {4, 3, 2}; vs[1] = {3, 3, 2}; *nv = 2;
+  } else if (R == 1) {
     // rows of 64 positions: half the ring bytes of R = 2, so the FP64 residual fits more
     // waves and a deeper ring
     if (f64) {
@@ -655,11 +718,11 @@ void variants(int mode, Variant (&vs)[4], int* nv) {
 
 // The shape of a launch: a shape forced by the tuner's timing calls, else the tuned
 // table's entry, else the cost model.
-template <typename T, int R>
+template <typename T, int R, int RW>
 bool pick(int n, int count, int mode, int* which, int* kz, Variant* var) {
   Variant vs[4];
   int nv = 0;
-  variants<T, R>(mode, vs, &nv);
+  variants<T, R, RW>(mode, vs, &nv);
   if (nv == 0) return false;
   int w = -1, z = 0;
   if (tune_forced_stencil(&w, &z) ||
@@ -670,6 +733,11 @@ bool pick(int n, int count, int mode, int* which, int* kz, Variant* var) {
       *var = vs[w];
       return true;
     }
+  }
+  if constexpr (RW > 1) {
+    *kz = choose_short<RW>(n, count, vs, nv, which).kz;
+    *var = vs[*which];
+    return true;
   }
   int64_t best = INT64_MAX;
   for (int i = 0; i < nv; ++i) {
@@ -684,70 +752,100 @@ bool pick(int n, int count, int mode, int* which, int* kz, Variant* var) {
   return true;
 }
 
-template <typename T, int R, int MODE>
+template <typename T, int R, int RW, int MODE>
 hipError_t launch_mode(const T* x, const T* b, T* y, const Geom& g, const Bat& bt, double* part,
                        int64_t pstride, double* dot, hipStream_t st) {
   constexpr bool f64 = std::is_same<T, double>::value;
   int which = 0, kz = 8;
   Variant var{};
-  if (!pick<T, R>(g.n, bt.count, MODE, &which, &kz, &var)) return hipErrorNotSupported;
-  if constexpr (R == 1) {
+  if (!pick<T, R, RW>(g.n, bt.count, MODE, &which, &kz, &var)) return hipErrorNotSupported;
+  if constexpr (RW == 4) {
+    if (which == 0) return launch_m<T, R, RW, 3, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+    return launch_m<T, R, RW, 2, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+  } else if constexpr (RW == 2) {
+    if (which == 0) return launch_m<T, R, RW, 4, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+    return launch_m<T, R, RW, 3, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+  } else if constexpr (R == 1) {
     if constexpr (f64 && MODE == 1) {
-      if (which == 0) return launch_m<T, R, 6, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 1) return launch_m<T, R, 10, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 2) return launch_m<T, R, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      return launch_m<T, R, 8, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 0) return launch_m<T, R, 1, 6, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 1) return launch_m<T, R, 1, 10, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 2) return launch_m<T, R, 1, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      return launch_m<T, R, 1, 8, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
     }
     if constexpr (f64 && MODE != 1) {
-      if (which == 0) return launch_m<T, R, 10, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 1) return launch_m<T, R, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 2) return launch_m<T, R, 6, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      return launch_m<T, R, 6, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 0) return launch_m<T, R, 1, 10, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 1) return launch_m<T, R, 1, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 2) return launch_m<T, R, 1, 6, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      return launch_m<T, R, 1, 6, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
     }
     if constexpr (!f64 && MODE == 1) {
-      if (which == 0) return launch_m<T, R, 10, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 1) return launch_m<T, R, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 2) return launch_m<T, R, 10, 3, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      return launch_m<T, R, 8, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 0) return launch_m<T, R, 1, 10, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 1) return launch_m<T, R, 1, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 2) return launch_m<T, R, 1, 10, 3, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      return launch_m<T, R, 1, 8, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
     }
     if constexpr (!f64 && MODE != 1) {
-      if (which == 0) return launch_m<T, R, 10, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 1) return launch_m<T, R, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 2) return launch_m<T, R, 10, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      return launch_m<T, R, 8, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 0) return launch_m<T, R, 1, 10, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 1) return launch_m<T, R, 1, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 2) return launch_m<T, R, 1, 10, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      return launch_m<T, R, 1, 8, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
     }
   } else if constexpr (R == 2) {
-    if constexpr (f64 && MODE == 1) return launch_m<T, R, 6, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+    if constexpr (f64 && MODE == 1) return launch_m<T, R, 1, 6, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
     if constexpr (f64 && MODE != 1) {
-      if (which == 0) return launch_m<T, R, 10, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 1) return launch_m<T, R, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 2) return launch_m<T, R, 6, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      return launch_m<T, R, 6, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 0) return launch_m<T, R, 1, 10, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 1) return launch_m<T, R, 1, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 2) return launch_m<T, R, 1, 6, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      return launch_m<T, R, 1, 6, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
     }
     if constexpr (!f64 && MODE == 1) {
-      if (which == 0) return launch_m<T, R, 10, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 1) return launch_m<T, R, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 2) return launch_m<T, R, 10, 3, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      return launch_m<T, R, 8, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 0) return launch_m<T, R, 1, 10, 3, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 1) return launch_m<T, R, 1, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 2) return launch_m<T, R, 1, 10, 3, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      return launch_m<T, R, 1, 8, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
     }
     if constexpr (!f64 && MODE != 1) {
-      if (which == 0) return launch_m<T, R, 10, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 1) return launch_m<T, R, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      if (which == 2) return launch_m<T, R, 10, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
-      return launch_m<T, R, 8, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 0) return launch_m<T, R, 1, 10, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 1) return launch_m<T, R, 1, 8, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      if (which == 2) return launch_m<T, R, 1, 10, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
+      return launch_m<T, R, 1, 8, 4, MODE, 1>(x, b, y, g, bt, kz, part, pstride, dot, st);
     }
   } else {
-    if constexpr (!(f64 && MODE == 1)) return launch_m<T, R, 4, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
+    if constexpr (!(f64 && MODE == 1)) return launch_m<T, R, 1, 4, 4, MODE>(x, b, y, g, bt, kz, part, pstride, dot, st);
   }
   return hipErrorNotSupported;
 }
 
-template <typename T, int R>
+template <typename T, int R, int RW>
 hipError_t launch_r(const T* x, const T* b, T* y, const Geom& g, const Bat& bt, int mode,
                     double* part, int64_t pstride, double* dot, hipStream_t st) {
-  if (mode == 0) return launch_mode<T, R, 0>(x, b, y, g, bt, part, pstride, dot, st);
-  if (mode == 1) return launch_mode<T, R, 1>(x, b, y, g, bt, part, pstride, dot, st);
-  return launch_mode<T, R, 2>(x, b, y, g, bt, part, pstride, dot, st);
+  if (mode == 0) return launch_mode<T, R, RW, 0>(x, b, y, g, bt, part, pstride, dot, st);
+  if (mode == 1) return launch_mode<T, R, RW, 1>(x, b, y, g, bt, part, pstride, dot, st);
+  return launch_mode<T, R, RW, 2>(x, b, y, g, bt, part, pstride, dot, st);
+}
+
+// Calls f with the positions per lane and rows per wave of meshes of n elements: a wave of
+// 64 lanes spans a row of up to 64 R positions, or RW rows of 64 / RW (n <= 16: 4 rows,
+// n <= 32: 2).
+template <int R_, int RW_>
+struct Span {
+  static constexpr int R = R_, RW = RW_;
+};
+
+template <typename F>
+auto with_span(int n, F f) {
+  if (n <= 16) return f(Span<1, 4>());
+  if (n <= 32) return f(Span<1, 2>());
+  if (n <= 64) return f(Span<1, 1>());
+  if (n <= 128) return f(Span<2, 1>());
+  return f(Span<4, 1>());
+}
+
+template <typename T>
+bool pick_n(int n, int count, int mode, int* which, int* kz, Variant* var) {
+  return with_span(n, [&](auto sp) {
+    return pick<T, decltype(sp)::R, decltype(sp)::RW>(n, count, mode, which, kz, var);
+  });
 }
 
 }  // namespace
@@ -755,18 +853,17 @@ hipError_t launch_r(const T* x, const T* b, T* y, const Geom& g, const Bat& bt, 
 int stencil_max_n() { return 256; }
 // Below this size the one-thread-per-node kernel is used: n <= 32 for a single pair (the
 // plane kernel's few tiles lose to its launch there), n <= 16 for batches of four or more
-// pairs, where the tiles of all pairs fill the chip.
-int stencil_min_n(int count) { return count >= 4 ? 16 : 32; }
+// pairs, where the tiles of all pairs fill the chip, n <= 8 for 64 or more.
+int stencil_min_n(int count) { return count >= 64 ? 8 : count >= 4 ? 16 : 32; }
 
 // partial sums per pair of the dot mode (FP64): one per tile of the chosen launch
 int stencil_blocks(const Geom& g, int count) {
   if (g.n <= stencil_min_n(count) || g.n > stencil_max_n()) return 0;
   int which = 0, kz = 8;
   Variant var{};
-  const bool ok = (g.n <= 64)    ? pick<double, 1>(g.n, count, 2, &which, &kz, &var)
-                  : (g.n <= 128) ? pick<double, 2>(g.n, count, 2, &which, &kz, &var)
-                                 : pick<double, 4>(g.n, count, 2, &which, &kz, &var);
-  return ok ? tiling(g.n, var.nw, kz).ntiles : 0;
+  if (!pick_n<double>(g.n, count, 2, &which, &kz, &var)) return 0;
+  const int rw = with_span(g.n, [](auto sp) { return decltype(sp)::RW; });
+  return tiling(g.n, rw * var.nw, kz).ntiles;
 }
 
 // room for the partial sums of any launch shape (any variant, at least 2 planes per
@@ -778,44 +875,26 @@ int stencil_max_blocks(const Geom& g) {
 
 bool stencil_shape(int n, int elem, int mode, int count, int* variant, int* kz) {
   Variant var{};
-  if (n <= 64) {
-    if (elem == 8) return pick<double, 1>(n, count, mode, variant, kz, &var);
-    return pick<float, 1>(n, count, mode, variant, kz, &var);
-  }
-  if (n <= 128) {
-    if (elem == 8) return pick<double, 2>(n, count, mode, variant, kz, &var);
-    return pick<float, 2>(n, count, mode, variant, kz, &var);
-  }
-  if (elem == 8) return pick<double, 4>(n, count, mode, variant, kz, &var);
-  return pick<float, 4>(n, count, mode, variant, kz, &var);
+  return elem == 8 ? pick_n<double>(n, count, mode, variant, kz, &var) : pick_n<float>(n, count, mode, variant, kz, &var);
 }
 
 int stencil_variant_count(int elem, int mode, int n) {
   Variant vs[4];
   int nv = 0;
-  if (n <= 64) {
-    if (elem == 8) variants<double, 1>(mode, vs, &nv);
-    else variants<float, 1>(mode, vs, &nv);
-  } else if (n <= 128) {
-    if (elem == 8) variants<double, 2>(mode, vs, &nv);
-    else variants<float, 2>(mode, vs, &nv);
-  } else {
-    if (elem == 8) variants<double, 4>(mode, vs, &nv);
-    else variants<float, 4>(mode, vs, &nv);
-  }
+  with_span(n, [&](auto sp) {
+    if (elem == 8) variants<double, decltype(sp)::R, decltype(sp)::RW>(mode, vs, &nv);
+    else variants<float, decltype(sp)::R, decltype(sp)::RW>(mode, vs, &nv);
+  });
   return nv;
 }
 
 template <typename T>
 hipError_t launch_stencil(const T* x, const T* b, T* y, const Geom& g, const Bat& bt, int mode,
                           double* part, int64_t pstride, double* dot, hipStream_t st) {
-  // rows span 64 R positions: R = 1 up to n = 64 (the position i = n of a row of 65 is
-  // written separately), R = 2 up to 128, R = 4 up to 256
-  if (g.n <= stencil_min_n(bt.count)) return hipErrorInvalidValue;
-  if (g.n <= 64) return launch_r<T, 1>(x, b, y, g, bt, mode, part, pstride, dot, st);
-  if (g.n <= 128) return launch_r<T, 2>(x, b, y, g, bt, mode, part, pstride, dot, st);
-  if (g.n <= 256) return launch_r<T, 4>(x, b, y, g, bt, mode, part, pstride, dot, st);
-  return hipErrorInvalidValue;
+  if (g.n <= stencil_min_n(bt.count) || g.n > stencil_max_n()) return hipErrorInvalidValue;
+  return with_span(g.n, [&](auto sp) {
+    return launch_r<T, decltype(sp)::R, decltype(sp)::RW>(x, b, y, g, bt, mode, part, pstride, dot, st);
+  });
 }
 
 template hipError_t launch_stencil<double>(const double*, const double*, double*, const Geom&,

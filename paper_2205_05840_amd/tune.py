@@ -36,9 +36,9 @@ def _stencil_cases(quick):
             for mode in modes:
                 yield n, prec, mode, 1
     if not quick:
-        # batched classes of the uneven-size form (the operator kernel from n > 16 at >= 4
+        # batched classes of the uneven-size form (the operator kernel from n > 8 at >= 64
         # pairs)
-        for n in (24, 32):
+        for n in (12, 16, 20, 24, 28, 32):
             for mode in (0, 1, 2):
                 yield n, "fp64", mode, 400
             for mode in (0, 1):
