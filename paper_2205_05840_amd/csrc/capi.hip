@@ -304,7 +304,7 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
       L.chunks.clear();
       int64_t groups = 0;
       for (const auto& sg : L.segs) groups += (sg.count + 15) / 16;
-      L.gpw = ndmg::patch_groups(groups * C.count, el);
+      L.gpw = ndmg::patch_groups(groups * C.count, C.count, el);
       int tuned_i = 0, tuned_b = 0;
       const bool tuned = cf.r == 0 && ndmg::tune_lookup(ndmg::kTunePatch, sizes[k], (int)el, 0, C.count, &tuned_i, &tuned_b) &&
                          tuned_i >= 1 && tuned_i <= 8 && tuned_b >= 1 && tuned_b <= 8;

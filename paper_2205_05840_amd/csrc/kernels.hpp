@@ -141,7 +141,12 @@ bool stencil_shape(int n, int elem, int mode, int count, int* variant, int* kz);
 // be resident at once, given the workgroups per CU that the kernel's registers allow
 // (6 in FP32 with buffer addressing, 3 in FP64 on a 256-CU MI355X), at most 8.
 inline int64_t patch_resident_blocks(size_t elem) { return (elem == 4 ? 6 : 3) * 256; }
-inline int patch_groups(int64_t groups, size_t elem) {
+// FP32 classes of 16 or more pairs: one, whose gathers, products and stores overlap best across
+// the many workgroups (V-cycle of 384 pairs: 16^3 533 -> 494 us with 1 instead of 4 groups, 24^3
+// 1238 -> 1196 and 32^3 2510 -> 2422 instead of 8; 48 pairs of 24^3 237 -> 230; 8 of 64^3 the
+// same; FP64 within the runs' spread).
+inline int patch_groups(int64_t groups, int count, size_t elem) {
+  if (elem == 4 && count >= 16) return 1;
   const int64_t resident = patch_resident_blocks(elem) * 4;   // waves
   const int64_t g = (groups + resident - 1) / resident;
   return (int)std::max<int64_t>(1, std::min<int64_t>(8, g));
