@@ -68,6 +68,7 @@ struct LevelHost {
   std::vector<ndmg::Segment> segs;
   std::vector<int> chunks;             // per chunk: segment | gpw << 16, first, wave step, group step
   int gpw = 1;                         // 16-vertex groups per wave of the patch kernel
+  bool one = false;                    // every chunk gives a wave one group
   std::vector<int64_t> map;            // coarsest level: padded offset of each unknown
   int nB = 0;
   // workspace offsets; per-pair arrays hold `count` copies, factors `nprob` copies
@@ -342,6 +343,8 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
           L.chunks.push_back(16);        // and takes consecutive groups
         }
       }
+      L.one = true;
+      for (size_t j = 0; j < L.chunks.size(); j += 4) L.one = L.one && ((L.chunks[j] >> 16) & 0x3fff) == 1;
       // One pair: the interior segment's chunks that run on one XCD (the kernel numbers
       // blocks with xcd_block: XCD x takes a contiguous range of chunks) share their
       // vertex range with the groups dealt out in turn, wave after wave, so that at any
@@ -541,6 +544,7 @@ ndmg::DSub level_dsub(ndmg_ctx* c, const LevelHost& L) {
   d.bofs = at<int64_t>(c, L.o_bofs);
   d.yrow = L.yrow;
   d.ntypes = L.ntypes;
+  d.one = L.one ? 1 : 0;
   d.r = L.bx.r;
   d.w = L.bx.w;
   d.cls = d.r > 0 ? at<int>(c, L.o_cls) : nullptr;

@@ -527,10 +527,13 @@ struct Mfma<float> {
 //   past the descriptor's range, and a load there returns zero.  The freed registers
 //   give FP32 6 waves per SIMD instead of 4 (80 registers; measured 34.1 -> 30.0 us
 //   at 128^3, FP64 50.6 -> 47.4 us, results bit for bit the same).
+// - ONE (FP32 with BUF, one group per wave in every chunk): without the second gather buffer
+//   8 waves per SIMD instead of 6 (52 registers for 80; V-cycle of 384 pairs of 32^3 2422 ->
+//   2372 us, 24^3 1196 -> 1189).
 // FP64: at least 3 waves per SIMD (168 registers), the residency patch_groups assumes;
 // FP32 without BUF fits 4 waves without the bound (asking for more makes it spill).
-template <typename T, int S, bool BUF>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 ? (BUF ? 5 : 1) : 3)
+template <typename T, int S, bool BUF, bool ONE>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 ? (ONE ? 8 : BUF ? 5 : 1) : 3)
     k_sm_patch(const T* __restrict__ gg, T* __restrict__ Y, const T* __restrict__ Sinv, DGeom g, DSub sub,
                Bat bt) {
   constexpr int NG = 6 * S * (4 * S - 3);
@@ -767,7 +770,9 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (BUF ? 5 : 1) : 3)
   // two buffers used in turn, so that no buffer is copied (a copy would wait for the
   // loads in flight); past the last group the gathers repeat it
   int c = 0;
-  if constexpr (BUF) {
+  if constexpr (ONE) {
+    product_store_buf(b0, yba);
+  } else if constexpr (BUF) {
     for (; c + 2 <= ngroups; c += 2) {
       gather_buf(c + 1, b1, ybb);
       product_store_buf(b0, yba);
@@ -2216,10 +2221,12 @@ template <typename T>
 void launch_sm_patch(const LevelPtrs<T>& L, const DSub& sub, const DGeom& dg, const Bat& bt, hipStream_t st) {
   const bool buf = smoother_buffers(dg, sub, bt, sizeof(T));
   const dim3 grid((unsigned)sub.nchunks, (unsigned)bt.count);
-  if (buf)
-    hipLaunchKernelGGL((k_sm_patch<T, 2, true>), grid, dim3(256), 0, st, L.gg, L.Y, L.Sinv, dg, sub, bt);
+  if (buf && sub.one && sizeof(T) == 4)
+    hipLaunchKernelGGL((k_sm_patch<T, 2, true, sizeof(T) == 4>), grid, dim3(256), 0, st, L.gg, L.Y, L.Sinv, dg, sub, bt);
+  else if (buf)
+    hipLaunchKernelGGL((k_sm_patch<T, 2, true, false>), grid, dim3(256), 0, st, L.gg, L.Y, L.Sinv, dg, sub, bt);
   else
-    hipLaunchKernelGGL((k_sm_patch<T, 2, false>), grid, dim3(256), 0, st, L.gg, L.Y, L.Sinv, dg, sub, bt);
+    hipLaunchKernelGGL((k_sm_patch<T, 2, false, false>), grid, dim3(256), 0, st, L.gg, L.Y, L.Sinv, dg, sub, bt);
 }
 
 template <typename T>

@@ -56,6 +56,7 @@ struct DSub {
   const int64_t* bofs;  // nB offsets of the subdomain boundary edges from its lower node
   int64_t yrow;         // row length of Y (its last 16 entries the zero run)
   int ntypes;           // S^{-1} matrices per problem
+  int one;              // every chunk gives a wave one group
   // coefficient boxes: r per axis of w subdomains each (r = 0: none); cls [2 r + 1]^3 pairs
   // {row position, type} per class triple of vertices (BoxPatches); A_T^{-1} and X_T then
   // hold one block per box (zero outside the domain)
