@@ -1265,6 +1265,157 @@ __global__ void __launch_bounds__(64) k_sm_pull_extend(const T* __restrict__ Y, 
   }
 }
 
+// Where the 48 boundary edges of T are summed when each subdomain sums the 18 it owns: the
+// owner T + q (q = bits x, y, z; an offset of 2 across the edge steps to the next subdomain)
+// and the edge's index among that owner's; slotW / slotC: its place among the 14 owned edges
+// that a neighbour across x or y reads from the same plane, and among the 4 that T - e_x and
+// T - e_y read from the plane above theirs (-1: none).
+struct EdgeOwners {
+  int q[48] = {}, k[48] = {}, e[18] = {}, slotW[18] = {}, slotC[18] = {};
+  bool floor[18] = {};   // lies in the lower z-face
+};
+constexpr EdgeOwners make_edge_owners() {
+  EdgeOwners t;
+  int nw = 0, nc = 0;
+  for (int k = 0; k < 18; ++k) {
+    const int d = kOI.d[k];
+    const bool fx = d != 0 && kOI.o[k][0] == 0, fy = d != 1 && kOI.o[k][1] == 0, fz = d != 2 && kOI.o[k][2] == 0;
+    t.floor[k] = fz;
+    t.slotW[k] = fx || fy ? nw++ : -1;
+    t.slotC[k] = fz && (fx || fy) ? nc++ : -1;
+    for (int e = 0; e < kBP.n; ++e)
+      if (kBP.d[e] == d && kBP.o[e][0] == kOI.o[k][0] && kBP.o[e][1] == kOI.o[k][1] && kBP.o[e][2] == kOI.o[k][2])
+        t.e[k] = e;
+  }
+  for (int e = 0; e < kBP.n; ++e) {
+    int l[3] = {};
+    for (int ax = 0; ax < 3; ++ax) {
+      const int up = ax != kBP.d[e] && kBP.o[e][ax] == 2;
+      t.q[e] |= up << ax;
+      l[ax] = kBP.o[e][ax] - 2 * up;
+    }
+    for (int k = 0; k < 18; ++k)
+      if (kOI.d[k] == kBP.d[e] && kOI.o[k][0] == l[0] && kOI.o[k][1] == l[1] && kOI.o[k][2] == l[2]) t.k[e] = k;
+  }
+  return t;
+}
+constexpr EdgeOwners kEO = make_edge_owners();
+
+// k_sm_pull_extend with fewer reads of Y, for planes of up to 16 x 16 subdomains: a block takes
+// one plane (c) of a pair.  Each lane sums the 18 interface edges its subdomain owns and the 8
+// of the plane above that lie in its upper face (84 loads of Y instead of 144) and takes the
+// other 22 of its boundary from the lanes across x and y through LDS.  The one-subdomain-per-
+// lane form is bound by its L1 accesses (61 % of the cycles; 2.4 TB/s from HBM).  V-cycle of
+// 384 pairs, FP32: 32^3 2356 -> 2177 us, 24^3 1175 -> 1095, 16^3 487 -> 441; FP64 3604 -> 3364,
+// 1803 -> 1706, 707 -> 678.  Marching c with sums kept for the next plane was slower (32^3 FP32,
+// 2 planes per block 2235, 4 2290: fewer waves), as were tiles with halos of larger planes
+// (128^3 FP32 352 -> 421).
+constexpr int kPullPlane = 16;
+template <typename T>
+__global__ void __launch_bounds__(kPullPlane* kPullPlane)
+    k_sm_pull_plane(const T* __restrict__ Y, const T* __restrict__ r, T* __restrict__ z, const T* __restrict__ XT,
+                    const T* __restrict__ ATinv, DGeom g, DSub sub, T eta, int assign, Bat bt) {
+  constexpr int NB = 48, NPAD = 64, NL = kPullPlane * kPullPlane;
+  constexpr bool kInPlace = sizeof(T) == 4;   // (as in k_sm_pull_extend)
+  __shared__ T sW[14][NL];
+  __shared__ T sC[4][NL];
+  __shared__ T lX[kInPlace ? 1 : 6 * NB];
+  __shared__ T lA[kInPlace ? 1 : 36];
+  const int nH = sub.nH;
+  const int bid = xcd_block(blockIdx.x, gridDim.x);
+  const int pair = bid / nH, c = bid - pair * nH;
+  if (inactive(bt, pair)) return;
+  const T* __restrict__ gX = XT + (int64_t)(pair / bt.nrhs) * 6 * NB;
+  const T* __restrict__ gA = ATinv + (int64_t)(pair / bt.nrhs) * 36;
+  const int t = threadIdx.x;
+  if constexpr (!kInPlace) {
+    for (int e = t; e < 6 * NB; e += blockDim.x) lX[e] = gX[e];
+    if (t < 36) lA[t] = gA[t];
+  }
+  auto sX = [&](int i) -> T {
+    if constexpr (kInPlace) return gX[i];
+    else return lX[i];
+  };
+  auto sA = [&](int i) -> T {
+    if constexpr (kInPlace) return gA[i];
+    else return lA[i];
+  };
+  const bool own = t < nH * nH;
+  const int a = own ? t % nH : 0, b = own ? t / nH : 0;   // (lanes past the plane sum for subdomain (0, 0))
+  const bool hx = a + 1 < nH, hy = b + 1 < nH;            // (the domain's upper faces: zero)
+  const int tx = own && hx ? t + 1 : t, ty = own && hy ? t + nH : t, txy = own && hx && hy ? t + nH + 1 : t;
+  const int64_t voff = (int64_t)pair * vlen(g);
+  r += voff;
+  z += voff;
+  const char* __restrict__ Yb = reinterpret_cast<const char*>(Y + (int64_t)pair * sub.yrow * NPAD);
+  const int64_t rowb = sub.yrow * (int64_t)sizeof(T);
+  // (the plane above the last: its vertices lie past the domain, and its sums are not used)
+  unsigned cb[12];
+#pragma unroll
+  for (int q = 0; q < 12; ++q)
+    cb[q] = (unsigned)y_pos(nH, sub.bpatch, a + (q & 1), b + ((q >> 1) & 1), min(c + (q >> 2), nH)) * (unsigned)sizeof(T);
+  const int64_t base = lin(g, 2 * a, 2 * b, 2 * c);
+  int64_t ioff[6];
+  interior_offsets_s2(g, base, ioff);
+  T zo[24], rI[6];
+#pragma unroll
+  for (int m = 0; m < 24; ++m) zo[m] = T(0);
+  if (!assign) {
+#pragma unroll
+    for (int m = 0; m < 6; ++m) zo[m] = z[ioff[m]];
+#pragma unroll
+    for (int k = 0; k < 18; ++k) zo[6 + k] = z[kOI.d[k] * g.B + base + lin(g, kOI.o[k][0], kOI.o[k][1], kOI.o[k][2])];
+  }
+#pragma unroll
+  for (int m = 0; m < 6; ++m) rI[m] = r[ioff[m]];
+  const bool top = c + 1 == nH;
+  T wc[18], wn[18];
+#pragma unroll
+  for (int k = 0; k < 18; ++k) {
+    const int e = kEO.e[k];
+    T acc = T(0), up = T(0);
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+      if (m < kBP.ncand[e]) {
+        acc += *reinterpret_cast<const T*>(Yb + kBP.slot[e][m] * rowb + cb[kBP.corner[e][m]]);
+        if (kEO.floor[k]) up += *reinterpret_cast<const T*>(Yb + kBP.slot[e][m] * rowb + cb[4 + kBP.corner[e][m]]);
+      }
+    wc[k] = acc;
+    wn[k] = top ? T(0) : up;
+  }
+#pragma unroll
+  for (int k = 0; k < 18; ++k) {
+    if (kEO.slotW[k] >= 0) sW[kEO.slotW[k]][t] = wc[k];
+    if (kEO.slotC[k] >= 0) sC[kEO.slotC[k]][t] = wn[k];
+  }
+  __syncthreads();
+  if (!own) return;
+  T wv[NB];
+#pragma unroll
+  for (int e = 0; e < NB; ++e) {
+    const int q = kEO.q[e], k = kEO.k[e];
+    if (q == 0) wv[e] = wc[k];
+    else if (q == 4) wv[e] = wn[k];
+    else if (q == 1) wv[e] = hx ? sW[kEO.slotW[k]][tx] : T(0);
+    else if (q == 2) wv[e] = hy ? sW[kEO.slotW[k]][ty] : T(0);
+    else if (q == 3) wv[e] = hx && hy ? sW[kEO.slotW[k]][txy] : T(0);
+    else if (q == 5) wv[e] = hx ? sC[kEO.slotC[k]][tx] : T(0);
+    else wv[e] = hy ? sC[kEO.slotC[k]][ty] : T(0);
+  }
+#pragma unroll
+  for (int m = 0; m < 6; ++m) {
+    T q6 = T(0), zi = T(0);
+#pragma unroll
+    for (int e = 0; e < NB; ++e) q6 += sX(m * NB + e) * wv[e];
+#pragma unroll
+    for (int s2 = 0; s2 < 6; ++s2) zi += sA(m * 6 + s2) * rI[s2];
+    z[ioff[m]] = zo[m] + eta * (zi - q6);
+  }
+#pragma unroll
+  for (int k = 0; k < 18; ++k)
+    z[kOI.d[k] * g.B + base + lin(g, kOI.o[k][0], kOI.o[k][1], kOI.o[k][2])] = zo[6 + k] + eta * wc[k];
+}
+
 // ---------------------------------------------------------------------------------
 // the V-cycle from one level down as a dense matrix per problem
 // ---------------------------------------------------------------------------------
@@ -2266,6 +2417,11 @@ hipError_t launch_smooth(const T* r, T* z, const LevelPtrs<T>& L, const DSub& su
   if (sub.r > 0)
     hipLaunchKernelGGL((k_sm_pull_extend<T, true>), dim3((unsigned)(nbp * bt.count)), dim3(64), 0, st, L.Y, r, z, L.XT,
                        L.ATinv, dg, sub, (T)eta, assign, bt, nbp, 0);
+  else if (sub.nH <= kPullPlane && bt.count >= 8)
+    // (8 pairs of 32^3 FP32 135 us either way, FP64 163 -> 159; fewer pairs fill too few units)
+    hipLaunchKernelGGL((k_sm_pull_plane<T>), dim3((unsigned)(sub.nH * bt.count)),
+                       dim3((unsigned)((sub.nH * sub.nH + 63) / 64 * 64)), 0, st, L.Y, r, z, L.XT, L.ATinv, dg, sub,
+                       (T)eta, assign, bt);
   else
     hipLaunchKernelGGL((k_sm_pull_extend<T, false>), eg, dim3(64), 0, st, L.Y, r, z, L.XT, L.ATinv, dg, sub, (T)eta,
                        assign, bt, nbs, packed);
