@@ -69,12 +69,16 @@ class _Context:
         self._last = self._bound = self.stream   # stream of the latest work; the library's stream
 
     def _bind(self, stream):
-        """Calls that follow enqueue on `stream`, after the context's earlier work."""
-        if self._last != stream and not torch.cuda.is_current_stream_capturing():
-            stream.wait_stream(self._last)
+        """Calls that follow enqueue on `stream`, after the context's earlier work.  Under a
+        capture nothing runs yet: the latest work stays what the next call waits for (a
+        replay is the caller's to order against other calls, as any graph's)."""
         if self._bound != stream:
             _lib.ndmg_set_stream(self.ctx, stream.cuda_stream)
             self._bound = stream
+        if torch.cuda.is_current_stream_capturing():
+            return
+        if self._last != stream:
+            stream.wait_stream(self._last)
         self._last = stream
 
     def _run(self, fn, *args, waits=False):

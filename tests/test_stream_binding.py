@@ -1,0 +1,86 @@
+"""Which stream a context's calls go to and what they wait for, on a model of streams (no GPU).
+
+A model stream knows the calls that are ordered before its next one; waiting for another stream
+adds what that one knows.  Every eager call of a context shares its level buffers with the
+calls before it, so it must know all of them, whatever streams they ran on."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2205_05840_amd import _lib, solver  # noqa: E402
+
+
+class Stream:
+    def __init__(self, world, handle):
+        self.world, self.cuda_stream = world, handle
+        self.known = set()
+        world.streams[handle] = self
+
+    def wait_stream(self, other):
+        self.known |= other.known
+
+    def synchronize(self):
+        pass
+
+
+class World:
+    """The streams, the caller's current one, the library's bound one and the calls made."""
+
+    def __init__(self, monkeypatch):
+        self.streams, self.calls, self.capturing = {}, [], None
+        self.current = Stream(self, 0)
+        mp = monkeypatch
+        mp.setattr(torch.cuda, "Stream", lambda device=None: Stream(self, 1000 + len(self.streams)))
+        mp.setattr(torch.cuda, "current_stream", lambda device=None: self.current)
+        mp.setattr(torch.cuda, "is_current_stream_capturing", lambda: self.capturing is self.current)
+        mp.setattr(_lib, "ndmg_set_stream", self.set_stream)
+        empty = torch.empty
+        mp.setattr(torch, "empty", lambda *a, device=None, **k: empty(*a, **k))
+        self.ctx = solver._Context()
+        self.ctx._alloc(16, "cuda:0")
+        self.ctx.ctx = 1
+        self.bound = self.ctx.stream   # (setup passes the context's own stream)
+
+    def set_stream(self, ctx, handle):
+        self.bound = self.streams[handle]
+
+    def fn(self, ctx, name):
+        """A library call: its name goes into what its stream knows."""
+        st = self.bound
+        if not self.capturing:
+            self.calls.append((name, st, set(st.known)))
+            st.known.add(name)
+        return name
+
+    def eager_calls_are_ordered(self):
+        for i, (name, _, known) in enumerate(self.calls):
+            missing = {n for n, _, _ in self.calls[:i]} - known
+            assert not missing, (name, missing)
+
+
+@pytest.fixture
+def world(monkeypatch):
+    w = World(monkeypatch)
+    yield w
+    w.ctx.ctx = None   # (no library context behind it)
+
+
+def test_steps_and_solves_follow_each_other(world):
+    a, b = Stream(world, 11), Stream(world, 13)
+    for i, (s, solve) in enumerate([(a, 0), (b, 0), (b, 1), (a, 0), (a, 0), (b, 1), (b, 0)]):
+        world.current = s
+        (world.ctx._run if solve else world.ctx._step)(world.fn, f"call {i}")
+        assert world.calls[-1][1] is (world.ctx.stream if solve else s)
+    world.eager_calls_are_ordered()
+
+
+@pytest.mark.parametrize("after", ["step", "solve"])
+def test_work_before_a_capture_is_waited_for_after_it(world, after):
+    a, b, c = Stream(world, 11), Stream(world, 13), Stream(world, 17)
+    world.current = a
+    world.ctx._step(world.fn, "before")
+    world.current = world.capturing = b   # (a raw capture: nothing has waited for a)
+    world.ctx._step(world.fn, "captured")
+    world.capturing, world.current = None, c
+    (world.ctx._step if after == "step" else world.ctx._run)(world.fn, "after")
+    world.eager_calls_are_ordered()
