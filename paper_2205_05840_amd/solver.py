@@ -63,7 +63,8 @@ class _Context:
         self._ws_ptr = (self.ws.data_ptr() + 255) // 256 * 256
         # solves run on a stream of the context's own (default priority; graph capture needs a
         # non-null stream), ordered after the caller's current stream, which waits for them;
-        # single steps (apply, vcycle, ...) go straight to the caller's current stream
+        # single steps (apply, vcycle, ...) go straight to the caller's current stream, if
+        # it is one that torch keeps for the life of the process
         self.stream = torch.cuda.Stream(device=self.device)
         self.stream.wait_stream(torch.cuda.current_stream(self.device))
         self._last = self._bound = self.stream   # stream of the latest work; the library's stream
@@ -98,10 +99,13 @@ class _Context:
     def _step(self, fn, *args):
         """A call on the caller's current stream.  While that is being captured into a graph
         the context's own stream joins the capture instead: work enqueued on other streams
-        before cannot be waited for there."""
-        if torch.cuda.is_current_stream_capturing():
+        before cannot be waited for there.  A stream that torch did not make (its number is
+        then its handle) may be destroyed after its work: it is not kept between calls, the
+        step takes the context's own stream."""
+        cur = torch.cuda.current_stream(self.device)
+        if torch.cuda.is_current_stream_capturing() or (cur.cuda_stream and cur.stream_id == cur.cuda_stream):
             return self._run(fn, *args)
-        self._bind(torch.cuda.current_stream(self.device))
+        self._bind(cur)
         return fn(self.ctx, *args)
 
     def close(self):

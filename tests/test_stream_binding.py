@@ -11,16 +11,20 @@ from paper_2205_05840_amd import _lib, solver  # noqa: E402
 
 
 class Stream:
-    def __init__(self, world, handle):
+    """torch numbers its own streams; one made elsewhere is numbered by its handle."""
+
+    def __init__(self, world, handle, external=False):
         self.world, self.cuda_stream = world, handle
-        self.known = set()
+        self.stream_id = handle if external else len(world.streams)
+        self.known, self.alive = set(), True
         world.streams[handle] = self
 
     def wait_stream(self, other):
+        assert self.alive and other.alive, "a destroyed stream"
         self.known |= other.known
 
     def synchronize(self):
-        pass
+        assert self.alive, "a destroyed stream"
 
 
 class World:
@@ -47,6 +51,7 @@ class World:
     def fn(self, ctx, name):
         """A library call: its name goes into what its stream knows."""
         st = self.bound
+        assert st.alive, "a destroyed stream"
         if not self.capturing:
             self.calls.append((name, st, set(st.known)))
             st.known.add(name)
@@ -84,3 +89,16 @@ def test_work_before_a_capture_is_waited_for_after_it(world, after):
     world.capturing, world.current = None, c
     (world.ctx._step if after == "step" else world.ctx._run)(world.fn, "after")
     world.eager_calls_are_ordered()
+
+
+def test_a_stream_of_the_caller_may_end_after_its_work(world):
+    ext = Stream(world, 4096, external=True)
+    world.current = ext
+    world.ctx._step(world.fn, "first")
+    assert "first" in ext.known   # what the caller does next on it follows the step
+    ext.alive = False             # synchronised and destroyed by the caller
+    world.current = Stream(world, 11)
+    world.ctx._step(world.fn, "second")
+    world.ctx._run(world.fn, "third")
+    world.eager_calls_are_ordered()
+    world.ctx._last.synchronize()   # (as closing the context does)
