@@ -3,6 +3,8 @@
 PyTorch supplies device memory (the workspace and the vectors) and the stream; every
 computation runs in libndmg.so.
 """
+import contextlib
+
 import numpy as np
 import torch
 
@@ -82,19 +84,27 @@ class _Context:
             stream.wait_stream(self._last)
         self._last = stream
 
+    def _on_device(self):
+        """The context's device as the current one: the default stream, whose handle is 0, is
+        the current device's."""
+        if torch.cuda.current_device() == self.device.index:
+            return contextlib.nullcontext()
+        return torch.cuda.device(self.device)
+
     def _run(self, fn, *args, waits=False):
         """A call on the context's own stream; waits: the call returns with its work done."""
-        cur = torch.cuda.current_stream(self.device)
-        self.stream.wait_stream(cur)
-        self._bind(self.stream)
-        done = False
-        try:
-            res = fn(self.ctx, *args)
-            done = waits
-            return res
-        finally:
-            if not done:
-                cur.wait_stream(self.stream)
+        with self._on_device():
+            cur = torch.cuda.current_stream(self.device)
+            self.stream.wait_stream(cur)
+            self._bind(self.stream)
+            done = False
+            try:
+                res = fn(self.ctx, *args)
+                done = waits
+                return res
+            finally:
+                if not done:
+                    cur.wait_stream(self.stream)
 
     def _step(self, fn, *args):
         """A call on the caller's current stream.  While that is being captured into a graph
@@ -102,11 +112,12 @@ class _Context:
         before cannot be waited for there.  A stream that torch did not make (its number is
         then its handle) may be destroyed after its work: it is not kept between calls, the
         step takes the context's own stream."""
-        cur = torch.cuda.current_stream(self.device)
-        if torch.cuda.is_current_stream_capturing() or (cur.cuda_stream and cur.stream_id == cur.cuda_stream):
-            return self._run(fn, *args)
-        self._bind(cur)
-        return fn(self.ctx, *args)
+        with self._on_device():
+            cur = torch.cuda.current_stream(self.device)
+            if torch.cuda.is_current_stream_capturing() or (cur.cuda_stream and cur.stream_id == cur.cuda_stream):
+                return self._run(fn, *args)
+            self._bind(cur)
+            return fn(self.ctx, *args)
 
     def close(self):
         if getattr(self, "ctx", None) is not None:

@@ -27,16 +27,30 @@ class Stream:
         assert self.alive, "a destroyed stream"
 
 
+class OnDevice:
+    def __init__(self, world, index):
+        self.world, self.index = world, index
+
+    def __enter__(self):
+        self.before, self.world.device = self.world.device, self.index
+
+    def __exit__(self, *exc):
+        self.world.device = self.before
+
+
 class World:
     """The streams, the caller's current one, the library's bound one and the calls made."""
 
     def __init__(self, monkeypatch):
         self.streams, self.calls, self.capturing = {}, [], None
+        self.device = 0   # the current device
         self.current = Stream(self, 0)
         mp = monkeypatch
         mp.setattr(torch.cuda, "Stream", lambda device=None: Stream(self, 1000 + len(self.streams)))
         mp.setattr(torch.cuda, "current_stream", lambda device=None: self.current)
         mp.setattr(torch.cuda, "is_current_stream_capturing", lambda: self.capturing is self.current)
+        mp.setattr(torch.cuda, "current_device", lambda: self.device)
+        mp.setattr(torch.cuda, "device", lambda d: OnDevice(self, torch.device(d).index))
         mp.setattr(_lib, "ndmg_set_stream", self.set_stream)
         empty = torch.empty
         mp.setattr(torch, "empty", lambda *a, device=None, **k: empty(*a, **k))
@@ -102,3 +116,20 @@ def test_a_stream_of_the_caller_may_end_after_its_work(world):
     world.ctx._run(world.fn, "third")
     world.eager_calls_are_ordered()
     world.ctx._last.synchronize()   # (as closing the context does)
+
+
+@pytest.mark.parametrize("call", ["_step", "_run"])
+def test_calls_run_on_the_context_s_device(world, call):
+    """(the default stream's handle, 0, names the current device's: a launch there must find the
+    context's device current)"""
+    world.ctx.device = torch.device("cuda:1")
+    at = []
+
+    def fn(ctx):
+        at.append(world.device)
+
+    for current in (0, 1):
+        world.device = current
+        getattr(world.ctx, call)(fn)
+        assert world.device == current
+    assert at == [1, 1]
