@@ -4,6 +4,7 @@ PyTorch supplies device memory (the workspace and the vectors) and the stream; e
 computation runs in libndmg.so.
 """
 import contextlib
+import threading
 
 import numpy as np
 import torch
@@ -70,6 +71,9 @@ class _Context:
         self.stream = torch.cuda.Stream(device=self.device)
         self.stream.wait_stream(torch.cuda.current_stream(self.device))
         self._last = self._bound = self.stream   # stream of the latest work; the library's stream
+        # the choice of stream and the launches on it are one step: calls from several threads
+        # run one after the other
+        self._lock = threading.RLock()
 
     def _bind(self, stream):
         """Calls that follow enqueue on `stream`, after the context's earlier work.  Under a
@@ -93,7 +97,7 @@ class _Context:
 
     def _run(self, fn, *args, waits=False):
         """A call on the context's own stream; waits: the call returns with its work done."""
-        with self._on_device():
+        with self._lock, self._on_device():
             cur = torch.cuda.current_stream(self.device)
             self.stream.wait_stream(cur)
             self._bind(self.stream)
@@ -112,7 +116,7 @@ class _Context:
         before cannot be waited for there.  A stream that torch did not make (its number is
         then its handle) may be destroyed after its work: it is not kept between calls, the
         step takes the context's own stream."""
-        with self._on_device():
+        with self._lock, self._on_device():
             cur = torch.cuda.current_stream(self.device)
             if torch.cuda.is_current_stream_capturing() or (cur.cuda_stream and cur.stream_id == cur.cuda_stream):
                 return self._run(fn, *args)

@@ -3,6 +3,8 @@
 A model stream knows the calls that are ordered before its next one; waiting for another stream
 adds what that one knows.  Every eager call of a context shares its level buffers with the
 calls before it, so it must know all of them, whatever streams they ran on."""
+import threading
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -47,7 +49,8 @@ class World:
         self.current = Stream(self, 0)
         mp = monkeypatch
         mp.setattr(torch.cuda, "Stream", lambda device=None: Stream(self, 1000 + len(self.streams)))
-        mp.setattr(torch.cuda, "current_stream", lambda device=None: self.current)
+        self.mine = threading.local()   # a thread's own current stream
+        mp.setattr(torch.cuda, "current_stream", lambda device=None: getattr(self.mine, "stream", self.current))
         mp.setattr(torch.cuda, "is_current_stream_capturing", lambda: self.capturing is self.current)
         mp.setattr(torch.cuda, "current_device", lambda: self.device)
         mp.setattr(torch.cuda, "device", lambda d: OnDevice(self, torch.device(d).index))
@@ -133,3 +136,33 @@ def test_calls_run_on_the_context_s_device(world, call):
         getattr(world.ctx, call)(fn)
         assert world.device == current
     assert at == [1, 1]
+
+
+def test_calls_from_two_threads_keep_their_streams(world):
+    """A second thread's step, let in between the first one's choice of stream and its launch
+    (if the context lets it), must not take the stream from under it."""
+    a, b = Stream(world, 11), Stream(world, 13)
+    bind, between, done = world.set_stream, threading.Event(), threading.Event()
+
+    def set_stream(ctx, handle):
+        bind(ctx, handle)
+        if handle == a.cuda_stream:
+            between.set()
+            done.wait(0.5)   # (a context that makes the second thread wait lets this time out)
+
+    _lib.ndmg_set_stream = set_stream   # (restored by the fixture)
+
+    def second():
+        world.mine.stream = b
+        between.wait(5)
+        world.ctx._step(world.fn, "second")
+        done.set()
+
+    t = threading.Thread(target=second)
+    t.start()
+    world.mine.stream = a
+    world.ctx._step(world.fn, "first")
+    t.join(5)
+    assert not t.is_alive()
+    assert {name: st for name, st, _ in world.calls} == {"first": a, "second": b}
+    world.eager_calls_are_ordered()
