@@ -171,6 +171,112 @@ __global__ void __launch_bounds__(256) k_gemm(GemmArgs<T> a, Bat bt) {
   }
 }
 
+// The same product for FP32 launches of many units.  Blocks of 64 units against 64 rows: wave w
+// takes rows rb 64 + 16 w .. + 15 for all 64 units (lane = unit), so the block reads its rows
+// of the matrix once per 64 units instead of once per 16.  The k dimension goes in chunks of
+// 32: the block stages the gathered inputs (32 x 64 units) and the chunk of M for its 64 rows
+// (32 x 64, k-major, coalesced rows of M) in LDS, every load issued before any is waited for
+// (an absent slot reads the unit's own anchor and is zeroed after the load); the next chunk's
+// loads are in flight while the current one is multiplied.  Sums run in k order, as above.
+// With enough blocks to hide the round trips, k_gemm is bound by the blocks in turn (edge
+// spaces, 64^3 x 4: patch products 47.7 us on half as many units per block, 24.3 here) or by
+// its reads of the matrix from L2 (s = 4, K = 320); in FP64 its longer products hide them.
+template <typename T, int MODE>
+__global__ void __launch_bounds__(256) k_gemm_wide(GemmArgs<T> a, Bat bt) {
+  constexpr int KC = 32;               // k per chunk
+  constexpr int VX = KC * 64 / 256;    // gathered inputs per thread and chunk (8)
+  constexpr int VM = KC * 64 / 256;    // values of M per thread and chunk (8)
+  static_assert(KC == 256 / 8 && VM == 8, "M staging: 8 threads of 8 values per k-row of 64 rows");
+  const int pair = blockIdx.y;
+  if (pair_inactive(bt, pair)) return;
+  const int chunk = blockIdx.x / a.nrb, rb = blockIdx.x - chunk * a.nrb;
+  const int type = a.chunks[4 * chunk], u0 = a.chunks[4 * chunk + 1], cnt = a.chunks[4 * chunk + 2];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool valid = lane < cnt;
+  const int64_t base = a.units[u0 + (valid ? lane : 0)];
+  const T* __restrict__ x = a.x + (int64_t)pair * a.vlen;
+  const T* __restrict__ x2 = a.x2 + (int64_t)pair * a.vlen;
+  const T* __restrict__ M = a.M + (int64_t)(pair / bt.nrhs) * a.mstride + (int64_t)type * a.npadK * a.npadR;
+  const int64_t* __restrict__ rin = a.relIn + (int64_t)type * a.npadK;
+  __shared__ T Xs[KC][64];
+  __shared__ __attribute__((aligned(16))) T Ms[KC][64];
+  // M staging: thread tid copies rows mr0 .. mr0 + 7 of k-row mk (8 consecutive values)
+  const int mk = tid >> 3, mr0 = (tid & 7) * 8;
+  const int rowb = rb * 64;
+  const int nrows = min(64, a.npadR - rowb);   // a multiple of 16
+  T xr[VX], mrg[VM];
+  auto load_chunk = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < VX; ++i) {
+      const int j = k0 + wave * VX + i;                 // uniform
+      const int jj = j < a.npadK ? j : 0;
+      const int64_t ro = rin[jj];
+      const bool ok = j < a.npadK && ro != kGenAbsent;
+      const T* __restrict__ src = j < a.ksplit ? x : x2;
+      const T v = src[base + (ok ? ro : 0)];
+      xr[i] = ok ? v : T(0);
+    }
+    const int k = k0 + mk;
+    const bool mok = k < a.npadK && mr0 < nrows;
+    const T* __restrict__ mp = M + (int64_t)(mok ? k : 0) * a.npadR + rowb + (mok ? mr0 : 0);
+#pragma unroll
+    for (int i = 0; i < VM; ++i) mrg[i] = mp[i];
+#pragma unroll
+    for (int i = 0; i < VM; ++i) mrg[i] = mok ? mrg[i] : T(0);
+  };
+  auto store_chunk = [&]() {
+#pragma unroll
+    for (int i = 0; i < VX; ++i) Xs[wave * VX + i][lane] = xr[i];
+#pragma unroll
+    for (int i = 0; i < VM; ++i) Ms[mk][mr0 + i] = mrg[i];
+  };
+  // wave w: 4 MFMA tiles of rows r0 .. r0 + 15 against units 16 t .. 16 t + 15
+  const int lr = lane & 15, lk = lane >> 4;
+  typename GMfma<T>::v4 acc[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) acc[t] = {T(0), T(0), T(0), T(0)};
+  const int r0 = wave * 16;   // within the block's rows
+  const bool rows_ok = r0 < nrows;
+  load_chunk(0);
+  for (int k0 = 0; k0 < a.npadK; k0 += KC) {
+    store_chunk();
+    __syncthreads();
+    if (k0 + KC < a.npadK) load_chunk(k0 + KC);   // in flight during the products
+    if (rows_ok) {
+      const int nks = min(KC, a.npadK - k0) / 4;   // npadK is a multiple of 16
+      for (int ks = 0; ks < nks; ++ks) {
+        const T av = Ms[4 * ks + lk][r0 + lr];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = GMfma<T>::mma(av, Xs[4 * ks + lk][16 * t + lr], acc[t]);
+      }
+    }
+    __syncthreads();
+  }
+  if (!rows_ok) return;
+  const int rg = rowb + r0;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int unit = 16 * t + lr;
+    if (unit >= cnt) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int row = GMfma<T>::row(lk, q);
+      const T val = acc[t][q];   // copied out before use as a scalar
+      if (MODE == kGemmToY) {
+        a.out[(int64_t)pair * a.ylen + (int64_t)(rg + row) * a.nunits + u0 + unit] = val;
+      } else {
+        const int64_t ro = a.relOut[(int64_t)type * a.npadR + rg + row];
+        if (ro == kGenAbsent) continue;
+        T* __restrict__ o = a.out + (int64_t)pair * a.vlen + a.units[u0 + unit] + ro;
+        const T v = a.scale * val;
+        *o = a.assign ? v : *o + v;
+      }
+    }
+  }
+}
+
 // Sum of up to four entries of src listed in codes (-1: none), in the listed order.
 template <typename T>
 __device__ __forceinline__ T pull4(const T* __restrict__ src, const int4 c) {
@@ -218,19 +324,39 @@ __global__ void __launch_bounds__(256) k_gen_pull(const T* __restrict__ Y, const
   }
 }
 
-// Unit groups per block: 4 / NU waves share the rows of a group, so few row tiles take many
-// groups.  Blocks along the rows: until the launch has four blocks per compute unit (64^3 s = 4
-// FP64 patch products 43 / 40 / 35 / 38 us with one, two, four and eight), or a wave one tile.
+// FP32 launches of 512 or more 64 x 64 blocks (two per compute unit) take the wide form
+// (V-cycles in us, k_gemm / wide from 512, 1024, 2048 blocks: edge spaces 64^3 x 4 456 / 421,
+// 428, 427, 10^3 x 400 255 / 231, 231, 232; s = 4 16^3 x 200 1785 / 1507, 1531, 1527, 64^3 x 4
+// 673 / 660, 652, 673; edge spaces at s = 4 16^3 x 64 292 / 240, 240, 292).
+// Else unit groups per block: 4 / NU waves share the rows of a group, so few row tiles take many
+// groups; twice as many from 256 chunks on, where blocks in turn, not their latency, bound the
+// launch (FP64, edge spaces: 64^3 x 4 648 -> 600 us, 10^3 x 400 353 -> 308; at s = 4 16^3 x 200
+// 837 -> 740), while LDS holds the gathered inputs.  Blocks along the rows: until the launch has
+// four blocks per compute unit (64^3 s = 4 FP64 patch products 43 / 40 / 35 / 38 us with one, two,
+// four and eight), or a wave one tile.
 template <typename T, int MODE>
 hipError_t gemm(GemmArgs<T> a, const Bat& bt, hipStream_t st) {
   if (a.nchunks <= 0) return hipSuccess;
   if (a.npadK % 16 || a.npadR % 16) return hipErrorInvalidValue;
-  const int ntiles = a.npadR / 16, nu = ntiles >= 4 ? 1 : (ntiles >= 2 ? 2 : 4);
+  const int64_t chunks = (int64_t)a.nchunks * bt.count;
+  if constexpr (sizeof(T) == 4) {
+    const int nrb = (a.npadR + 63) / 64;
+    if (chunks * nrb >= 512) {
+      a.nrb = nrb;
+      hipLaunchKernelGGL((k_gemm_wide<T, MODE>), dim3((unsigned)(a.nchunks * nrb), (unsigned)bt.count), dim3(256), 0,
+                         st, a, bt);
+      return hipGetLastError();
+    }
+  }
+  const size_t max_lds = 64 * 1024, lds1 = (size_t)a.npadK * 16 * sizeof(T);
+  const int ntiles = a.npadR / 16;
+  int nu = ntiles >= 4 ? 1 : (ntiles >= 2 ? 2 : 4);
+  if (chunks >= 256 && nu < 4 && 2 * nu * lds1 <= max_lds) nu *= 2;
   const int64_t sub = (int64_t)a.nchunks * (4 / nu);
   const int64_t want = (1024 + sub * bt.count - 1) / (sub * bt.count);
   a.nrb = (int)std::max<int64_t>(1, std::min<int64_t>(want, (ntiles + 4 / nu - 1) / (4 / nu)));
-  const size_t lds = (size_t)a.npadK * 16 * nu * sizeof(T);
-  if (lds > 64 * 1024) return hipErrorInvalidValue;
+  const size_t lds = nu * lds1;
+  if (lds > max_lds) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(sub * a.nrb), (unsigned)bt.count);
   if (nu == 1)
     hipLaunchKernelGGL((k_gemm<T, MODE, 1>), grid, dim3(256), lds, st, a, bt);
