@@ -998,9 +998,14 @@ template <typename T>
 int solve_coarse(ndmg_ctx* c, Cls& C, const T* g, T* z, const ndmg::Bat& bt, hipStream_t st) {
   const LevelHost& L = C.lv[0];
   if (L.map.empty()) return NDMG_OK;
-  // (A_0^{-1} is symmetric: the transposed form for many problems reads it as it is)
-  NDMG_HIP(ndmg::launch_dense_vcycle<T>(g, z, at<T>(c, L.o_A0), at<int64_t>(c, L.o_map), (int)L.map.size(), L.g.len, bt,
-                                        false, C.nprob >= 8, st));
+  // A_0^{-1} is symmetric: the transposed form (a row per thread) reads it as it is.  For many
+  // problems as for the dense levels, and for many pairs: its time is the chain over a row
+  // whatever their number, the other form's grows with them (one problem, FP64, us: N = 240,
+  // 16 / 40 / 300 right-hand sides 10.7 / 10.8 / 11.0 against 9.0 / 11.3 / 36; N = 756, 64 / 100 /
+  // 200 46.5 / 46.1 / 45.8 against 35.8 / 52.9 / 100).
+  const int N = (int)L.map.size();
+  NDMG_HIP(ndmg::launch_dense_vcycle<T>(g, z, at<T>(c, L.o_A0), at<int64_t>(c, L.o_map), N, L.g.len, bt, false,
+                                        C.nprob >= 8 || 8 * bt.count >= N, st));
   return NDMG_OK;
 }
 
