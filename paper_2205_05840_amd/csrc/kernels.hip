@@ -2115,11 +2115,14 @@ __global__ void __launch_bounds__(1024) k_pcg_check(double* __restrict__ scal, i
   __shared__ int sh[16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int c = 0;
-  // one wavefront per pair (its partials go out together; lane 0 then tests), one thread per
-  // pair where there are few partials: a chain of one memory round trip for up to 16 pairs
-  // (8 pairs of 512 partials one after the other by the whole block: 11.7 us; adjoint gradient
-  // of 8 right-hand sides at 64^3 47.6 -> 46.9 ms)
-  const bool wide = rr_n > 16 || count <= 16;
+  // one wavefront per pair (its partials go out together; lane 0 then tests) for up to 16 pairs,
+  // a chain of one memory round trip (8 pairs of 512 partials one after the other by the whole
+  // block: 11.7 us; adjoint gradient of 8 right-hand sides at 64^3 47.6 -> 46.9 ms), and beyond
+  // as long as a pair has as many partials as there are pairs; else one thread per pair, whose
+  // chain is its partials while the wavefronts' is the pairs over 16 (per CG iteration in us,
+  // wavefront / thread: 32^3 x 17 253 / 311, x 64 (64 partials) 602 / 612, 14^3 x 48 (43) 153.3 /
+  // 151.6, 24^3 x 100 (40) 458 / 451, 14^3 x 200 (20) 322 / 300)
+  const bool wide = count <= 16 || rr_n >= count;
   const int p0 = wide ? wave : (int)threadIdx.x, dp = (int)(wide ? blockDim.x >> 6 : blockDim.x);
   for (int p = p0; p < count; p += dp) {
     double* s = scal + (int64_t)p * kScalStride;
