@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "kernels.hpp"
@@ -1489,21 +1490,24 @@ __global__ void __launch_bounds__(256) k_dense_vcycle_t(const T* __restrict__ g,
     T acc[RC];
 #pragma unroll
     for (int r = 0; r < RC; ++r) acc[r] = T(0);
+    // the chain over the row, 16 loads at a time (8: N = 756, FP64 46 -> 38 us, N = 240, FP32
+    // 15.6 -> 11)
     int j = 0;
-    for (; j + 8 <= N; j += 8) {
-      T b[8];
+    auto steps = [&](auto width) {
+      constexpr int U = decltype(width)::value;
+      for (; j + U <= N; j += U) {
+        T b[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) b[u] = Bp[(int64_t)(j + u) * N + ic];
+        for (int u = 0; u < U; ++u) b[u] = Bp[(int64_t)(j + u) * N + ic];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int r = 0; r < RC; ++r) acc[r] += b[u] * sg[r * N + j + u];
-    }
-    for (; j < N; ++j) {
-      const T b = Bp[(int64_t)j * N + ic];
-#pragma unroll
-      for (int r = 0; r < RC; ++r) acc[r] += b * sg[r * N + j];
-    }
+          for (int r = 0; r < RC; ++r) acc[r] += b[u] * sg[r * N + j + u];
+      }
+    };
+    steps(std::integral_constant<int, 16>{});
+    steps(std::integral_constant<int, 4>{});
+    steps(std::integral_constant<int, 1>{});
     if (i < N) {
       const int64_t zi = map[i];
 #pragma unroll
