@@ -2319,8 +2319,10 @@ hipError_t launch_apply(const T* x, const T* b, T* y, const Geom& g, const Bat& 
                         hipStream_t st, bool pad) {
   // batches of four or more pairs take the plane-marching kernel from n = 17, of 64 or more
   // from n = 9, in both precisions, several rows per wave (residual of 400 pairs, FP32:
-  // 16^3 33 against 52 us one thread per node, 12^3 20 against 25)
-  const int min_n = stencil_min_n(bt.count);
+  // 16^3 33 against 52 us one thread per node, 12^3 20 against 25); the residual from n = 12:
+  // at 10^3, where 10 of 16 lanes work and the ring holds b as well, one thread per node (V-cycle
+  // of 400 pairs FP64 256 -> 241 us, FP32 189 -> 187; A x 21.1 us against 24)
+  const int min_n = mode == 1 ? std::max(11, stencil_min_n(bt.count)) : stencil_min_n(bt.count);
   // with a coefficient per cell the plane-marching kernel takes box grids of up to 8^3
   // (its factors in LDS); others, and the smaller levels, take the per-thread kernels
   if (g.n > min_n && g.n <= stencil_max_n()) {
