@@ -2426,8 +2426,10 @@ hipError_t launch_smooth(const T* r, T* z, const LevelPtrs<T>& L, const DSub& su
   if (sub.r > 0)
     hipLaunchKernelGGL((k_sm_pull_extend<T, true>), dim3((unsigned)(nbp * bt.count)), dim3(64), 0, st, L.Y, r, z, L.XT,
                        L.ATinv, dg, sub, (T)eta, assign, bt, nbp, 0);
-  else if (sub.nH <= kPullPlane && bt.count >= 8)
-    // (8 pairs of 32^3 FP32 135 us either way, FP64 163 -> 159; fewer pairs fill too few units)
+  else if (sub.nH <= kPullPlane && bt.count >= 8 && !(sizeof(T) == 8 && sub.nH <= 4 && bt.count >= 256))
+    // (8 pairs of 32^3 FP32 135 us either way, FP64 163 -> 159; fewer pairs fill too few units;
+    // many pairs of 8^3 in FP64 leave 48 lanes of a plane's wave idle and are not bound by the
+    // reads: V-cycle of 300 pairs 218 us by planes, 212 by subdomains; 100 pairs 107 / 109)
     hipLaunchKernelGGL((k_sm_pull_plane<T>), dim3((unsigned)(sub.nH * bt.count)),
                        dim3((unsigned)((sub.nH * sub.nH + 63) / 64 * 64)), 0, st, L.Y, r, z, L.XT, L.ATinv, dg, sub,
                        (T)eta, assign, bt);
