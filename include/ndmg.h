@@ -13,10 +13,11 @@
  * used by ndmg_curlcurl_form_noalloc, is the exception).  A context owns host metadata, a few pinned
  * host words for the convergence test and, when it holds several problem sizes, one
  * side stream and event per extra size.  All device work is enqueued on the stream
- * given at setup (work of extra sizes forks from it and joins back before a call
- * returns its last enqueued operation).  A context must not be used from two threads
- * at once.  Functions return NDMG_OK or one of the error codes below and never abort
- * or throw; ndmg_last_error() then describes the failure (per thread).
+ * given at setup or, later, to ndmg_set_stream (work of extra sizes forks from it and
+ * joins back before a call returns its last enqueued operation).  A context must not
+ * be used from two threads at once.  Functions return NDMG_OK or one of the error codes
+ * below and never abort or throw; ndmg_last_error() then describes the failure (per
+ * thread).
  *
  * Vector layout ("padded edge layout").  The mesh has n^3 cubes of side h = length/n.
  * An edge of direction d (0 = x, 1 = y, 2 = z) is addressed by (i, j, k): along axis
@@ -78,7 +79,8 @@ typedef struct ndmg_opts {
                            -1 (default): graphs unless the context holds one size
                            class whose finest level has n >= 64 (there the host
                            queues an iteration's launches faster than the device
-                           runs them) or n <= 12 (few launches per iteration)        */
+                           runs them), or n <= 12 with at most 256 pairs and no
+                           coefficient boxes or domain (few launches per iteration)  */
   int bottom_n;         /* levels with n_k <= bottom_n (at most 64) and the coarsest
                            solve run as one launch with one workgroup per (problem,
                            right-hand side); 0 (default): every level launches its
@@ -103,8 +105,9 @@ typedef struct ndmg_opts {
                            cell-by-cell form of eq. (fem) with its cell's alpha, the coarse
                            forms are the Galerkin restrictions of the fine one, and every
                            subdomain and patch gets the factors of its own alphas (any
-                           smoother and subdomain size; the gathered-product smoother on
-                           every level).  Single problems only (ndmg_setup, or one problem
+                           smoother and subdomain size; subdomains of 2 with the vertex
+                           smoother on its own kernels, the others on the gathered
+                           products).  Single problems only (ndmg_setup, or one problem
                            in ndmg_setup_batched); bottom_n must be 0; ndmg_export_factor
                            is refused.  ndmg_curlcurl_form then returns lam^T K_c u with
                            K_c = sum_T coef_T K_T, the derivative of A in alpha.          */

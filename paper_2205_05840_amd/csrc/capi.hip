@@ -1343,8 +1343,9 @@ void drop_graphs(ndmg_ctx* c) {
 // Graphs for the CG iterations: as asked, or (use_graphs -1) unless one size class makes eager
 // launches the faster ones: a finest level of n >= 64, whose iterations are long enough for
 // them to keep ahead of the device (64^3 FP64 5.40 against 5.56 ms per solve with graphs, FP32
-// equal, 48^3 4.17 against 3.93), or an iteration of a few launches (one_step: 8^3 0.50
-// against 0.63 to 0.73 ms, 12^3 1.22 against 1.27).
+// equal, 48^3 4.17 against 3.93; with 2 to 8 right-hand sides, s = 4, boxes and domains 0.4 to
+// 2.5 % faster, the FP32 edge spaces with one right-hand side 3.5 % slower), or an iteration of
+// a few launches (one_step: 8^3 0.50 against 0.63 to 0.73 ms, 12^3 1.22 against 1.27).
 bool use_graphs(const ndmg_ctx* c) {
   const Plan& pl = c->plan;
   if (pl.opts.use_graphs >= 0) return pl.opts.use_graphs != 0;

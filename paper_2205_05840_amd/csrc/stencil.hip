@@ -664,7 +664,12 @@ Choice choose_kz(int n, int count, Variant v) {
 // block's start included, and the fewest parts along k, at least RW, that give 768 blocks
 // (24^3, FP32 residual of 400 pairs: 12 planes 73 us, 24 planes 111, 6 planes 78; of 64
 // pairs 8 planes 17.2, 24 planes 27; 16 pairs FP64 apply: 2 planes 10.2, 8 planes 12.7;
-// 16^3, FP32 residual of 400 pairs: 4 planes 33, 8 planes 45).
+// 16^3, FP32 residual of 400 pairs: 4 planes 33, 8 planes 45).  With 400 pairs its
+// choice was the fastest of a sweep at 12^3 to 24^3; at 28^3 and 32^3 the variant with fewer waves
+// was, by 1.16 to 1.25 (FP64 residual 188 against 234 us at 28^3, 264 / 309 at 32^3), except for
+// the FP32 apply at 32^3 (8 planes instead of 16).  The tuner's table holds those for 64 pairs
+// and more; 4 to 63 pairs take this rule's shape, still faster than one row per wave (40 pairs of
+// 32^3, the operator's launches of a solve: 47 -> 19 us on average).
 template <int RW, typename VS>
 Choice choose_short(int n, int count, const VS& vs, int nv, int* which) {
   int best = INT_MAX, ntj = 1;
