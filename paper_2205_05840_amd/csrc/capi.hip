@@ -181,6 +181,30 @@ int check_opts(const ndmg_opts* o_in, ndmg_opts* o) {
   return NDMG_OK;
 }
 
+// Whether a level with coefficient boxes takes the box form of the vertex kernels (else the
+// generic smoother).  A small level does.  On larger ones the box form runs a workgroup per
+// class triple with patches and blocks per box, kept or not; the gathered products run one per
+// 64 patches of a type wherever they lie.  So it wins while a triple holds many patches, and
+// where there are few triples (V-cycle in us, box form / generic, FP32 and FP64): r = 4 at 128^3
+// 421 / 734, 649 / 1065 (721 triples of 381 patches); r = 8 at 64^3, every other box 171 / 179,
+// 233 / 210 (3688 of 7); r = 5 at 40^3 126 / 145, 150 / 150 (1323 of 7); r = 10 at 40^3, every
+// other box 143 / 119, 221 / 127 (7070 of 1), a rod of 2 x 2 89 / 99, 101 / 101 (517 of 1); r = 20 at
+// 80^3, a corner of 27 boxes 168 / 160, 198 / 162 (335 of 1, 8000 boxes to skip), r = 16 at 64^3
+// 129 / 130, 148 / 146 (4096 boxes).
+// Builds its patches; false (a level that the form cannot hold, too) leaves *out empty.
+bool box_form(const LevelHost& L, const ndmg::CoefBoxes& cf, bool boundary, int count, size_t elem,
+              ndmg::BoxPatches* out) {
+  const bool small = ndmg::small_level(L.sub.nH, count);
+  ndmg::BoxPatches b;
+  std::string err;
+  if ((!small && cf.r > 16) || !ndmg::build_box_patches(L.g, boundary, cf, &b, &err)) return false;
+  int64_t patches = 0;
+  for (const ndmg::Segment& q : b.segs) patches += q.count;
+  if (!small && (int64_t)b.segs.size() > (elem == 4 ? 500 + patches / 8 : 300 + patches / 10)) return false;
+  *out = std::move(b);
+  return true;
+}
+
 // Workspace layout of one size class; `take` hands out aligned offsets.
 template <typename Take>
 int plan_class(Cls& C, const Plan& pl, Take&& take) {
@@ -251,8 +275,10 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
       L.smoothed = true;
       L.sub = ndmg::make_sub(s, sizes[k]);
       std::string err;
-      if (pl.opts.smoother == NDMG_SMOOTHER_EDGE || s != 2) {
-        // the generic smoother: gathered products over subdomains and patches
+      if (pl.opts.smoother == NDMG_SMOOTHER_EDGE || s != 2 ||
+          (cf.r > 0 && !box_form(L, cf, pl.opts.boundary_patches != 0, C.count, pl.elem, &L.bx))) {
+        // the generic smoother: gathered products over subdomains and patches (which refuses what
+        // no smoother takes)
         L.gen = true;
         if (!ndmg::build_gen_tables(L.g, s, pl.opts.smoother == NDMG_SMOOTHER_EDGE ? 1 : 0,
                                     pl.opts.boundary_patches != 0, &L.gt, &err, cf))
@@ -290,8 +316,6 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
         continue;
       }
       if (cf.r > 0) {
-        if (!ndmg::build_box_patches(L.g, pl.opts.boundary_patches != 0, cf, &L.bx, &err))
-          return fail(NDMG_EINVAL, err);
         L.segs = L.bx.segs;
         L.yrow = L.bx.yrow;
         L.ntypes = (int)L.bx.geom.size();
