@@ -183,14 +183,22 @@ int check_opts(const ndmg_opts* o_in, ndmg_opts* o) {
 
 // Whether a level with coefficient boxes takes the box form of the vertex kernels (else the
 // generic smoother).  A small level does.  On larger ones the box form runs a workgroup per
-// class triple with patches and blocks per box, kept or not; the gathered products run one per
-// 64 patches of a type wherever they lie.  So it wins while a triple holds many patches, and
-// where there are few triples (V-cycle in us, box form / generic, FP32 and FP64): r = 4 at 128^3
-// 421 / 734, 649 / 1065 (721 triples of 381 patches); r = 8 at 64^3, every other box 171 / 179,
-// 233 / 210 (3688 of 7); r = 5 at 40^3 126 / 145, 150 / 150 (1323 of 7); r = 10 at 40^3, every
-// other box 143 / 119, 221 / 127 (7070 of 1), a rod of 2 x 2 89 / 99, 101 / 101 (517 of 1); r = 20 at
-// 80^3, a corner of 27 boxes 168 / 160, 198 / 162 (335 of 1, 8000 boxes to skip), r = 16 at 64^3
-// 129 / 130, 148 / 146 (4096 boxes).
+// class triple with patches (at least), and blocks per box, kept or not; the gathered products
+// run one per 64 patches of a type, wherever they lie.  So it wins where a triple holds many
+// patches (w >= 8 subdomains per box and axis, or r = 2 boxes), where nearly every triple has a
+// type of its own, and, by its fewer launches, while its workgroups stay few.  V-cycles in us,
+// box form / generic, FP32 and FP64 (r boxes per axis, k right-hand sides):
+//   r = 4, 128^3, two materials 421 / 734, 649 / 1065; r = 2, 64^3, k = 4 283 / 422, 371 / 602;
+//   r = 7, 56^3, k = 8, each box its own factor 1074 / 1204, 1980 / 2333; two materials
+//   1051 / 685, 1939 / 970;
+//   r = 8, 64^3, every other box (w = 4, 4200 workgroups) 171 / 179, 233 / 210; r = 6, 48^3, two
+//   materials (2621) 142 / 163, 181 / 185; r = 5, 40^3 (1573) 126 / 145, 150 / 150, k = 16 630 /
+//   552, 1075 / 816;
+//   r = 10, 40^3 (w = 2), a rod (597) 89 / 99, 101 / 101, a slab (1347) 96 / 103, 118 / 105, every
+//   other box (8070) 143 / 119, 221 / 127;
+//   r = 7, 14^3 (w = 1), k = 64, two materials (276 types, 1190) 502 / 581, 1085 / 1248, a corner
+//   (20 types, 110) 154 / 124, 210 / 173;
+//   r = 16, 64^3, a corner of 27 boxes 129 / 130, 148 / 146; r = 20, 80^3 168 / 160, 198 / 162.
 // Builds its patches; false (a level that the form cannot hold, too) leaves *out empty.
 bool box_form(const LevelHost& L, const ndmg::CoefBoxes& cf, bool boundary, int count, size_t elem,
               ndmg::BoxPatches* out) {
@@ -198,9 +206,16 @@ bool box_form(const LevelHost& L, const ndmg::CoefBoxes& cf, bool boundary, int 
   ndmg::BoxPatches b;
   std::string err;
   if ((!small && cf.r > 16) || !ndmg::build_box_patches(L.g, boundary, cf, &b, &err)) return false;
-  int64_t patches = 0;
-  for (const ndmg::Segment& q : b.segs) patches += q.count;
-  if (!small && (int64_t)b.segs.size() > (elem == 4 ? 500 + patches / 8 : 300 + patches / 10)) return false;
+  if (!small && b.w < 8 && b.r > 2) {
+    std::vector<int64_t> of_type(b.geom.size(), 0);
+    for (const ndmg::Segment& q : b.segs) of_type[q.type] += q.count;
+    int64_t chunks = 0, kept = 0;   // of the gathered patch products; boxes inside the domain
+    for (int64_t n : of_type) chunks += (n + 63) / 64;
+    for (int i = 0; i < cf.r * cf.r * cf.r; ++i) kept += cf.v[i] > 0.0;
+    const int64_t groups = (int64_t)b.segs.size() + 2 * kept;
+    const int64_t few = b.w >= 4 ? (elem == 4 ? 4500 : count == 1 ? 2700 : 1500) : (elem == 4 ? 2000 : 750);
+    if (9 * chunks < 2 * groups && groups * count > few) return false;
+  }
   *out = std::move(b);
   return true;
 }
