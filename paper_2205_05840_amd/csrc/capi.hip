@@ -82,6 +82,7 @@ struct LevelHost {
   // generic smoother (edge spaces, or subdomains of size 4): tables and factors
   bool gen = false;
   ndmg::GenTables gt;
+  int fillI = 64, fillP = 64;          // units of the fullest chunk of subdomains, of patches
   // coefficient boxes on the vertex smoother (subdomains of 2): patch classes, factors per box
   ndmg::BoxPatches bx;
   size_t o_cls = 0;
@@ -298,6 +299,13 @@ int plan_class(Cls& C, const Plan& pl, Take&& take) {
         if (!ndmg::build_gen_tables(L.g, s, pl.opts.smoother == NDMG_SMOOTHER_EDGE ? 1 : 0,
                                     pl.opts.boundary_patches != 0, &L.gt, &err, cf))
           return fail(NDMG_EINVAL, err);
+        auto fullest = [](const std::vector<int>& ch) {
+          int f = 1;
+          for (size_t i = 2; i < ch.size(); i += 4) f = std::max(f, ch[i]);
+          return f;
+        };
+        L.fillI = fullest(L.gt.chunksI);
+        L.fillP = fullest(L.gt.chunksP);
         L.o_r = take(vb);
         L.o_gg = take(vb);
         L.o_w = take(vb);
@@ -780,6 +788,7 @@ ndmg::GenLevel<T> gen_level(ndmg_ctx* c, const LevelHost& L) {
   Cd.npadR = tb.npadB;
   Cd.ylen = L.clenG;
   Cd.nunits = (int64_t)tb.unitsI.size();
+  Cd.fill = L.fillI;
   auto& Ex = G.ext;    // z_I = eta [A_T^{-1} | -X_T] [r_I ; w_dT]
   common(Ex);
   Ex.M = at<T>(c, L.o_gE);
@@ -793,6 +802,7 @@ ndmg::GenLevel<T> gen_level(ndmg_ctx* c, const LevelHost& L) {
   Ex.npadK = tb.npadE;
   Ex.npadR = tb.npadI;
   Ex.ylen = 0;
+  Ex.fill = L.fillI;
   auto& P = G.patch;   // y_P = S_P^{-1} g|Gamma_P
   common(P);
   P.M = at<T>(c, L.o_gS);
@@ -807,6 +817,7 @@ ndmg::GenLevel<T> gen_level(ndmg_ctx* c, const LevelHost& L) {
   P.npadR = tb.npadP;
   P.ylen = L.ylenG;
   P.nunits = (int64_t)tb.unitsP.size();
+  P.fill = L.fillP;
   G.C = at<T>(c, L.o_C);
   G.gg = at<T>(c, L.o_gg);
   G.Y = at<T>(c, L.o_Y);

@@ -70,9 +70,8 @@ __global__ void __launch_bounds__(256) k_gemm(GemmArgs<T> a, Bat bt) {
   T* Xs = reinterpret_cast<T*>(gemm_smem);   // [NU][npadK][16]
   const int pair = blockIdx.y;
   if (pair_inactive(bt, pair)) return;
-  constexpr int NSUB = 4 / NU;
   const int rb = blockIdx.x % a.nrb, sc = blockIdx.x / a.nrb;
-  const int chunk = sc / NSUB, sub = sc - chunk * NSUB;
+  const int chunk = sc / a.nsub, sub = sc - chunk * a.nsub;
   const int type = a.chunks[4 * chunk], u0 = a.chunks[4 * chunk + 1] + 16 * NU * sub;
   const int cnt = min(a.chunks[4 * chunk + 2] - 16 * NU * sub, 16 * NU);
   if (cnt <= 0) return;
@@ -331,9 +330,12 @@ __global__ void __launch_bounds__(256) k_gen_pull(const T* __restrict__ Y, const
 // Else unit groups per block: 4 / NU waves share the rows of a group, so few row tiles take many
 // groups; twice as many from 256 chunks on, where blocks in turn, not their latency, bound the
 // launch (FP64, edge spaces: 64^3 x 4 648 -> 600 us, 10^3 x 400 353 -> 308; at s = 4 16^3 x 200
-// 837 -> 740), while LDS holds the gathered inputs.  Blocks along the rows: until the launch has
-// four blocks per compute unit (64^3 s = 4 FP64 patch products 43 / 40 / 35 / 38 us with one, two,
-// four and eight), or a wave one tile.
+// 837 -> 740), while LDS holds the gathered inputs, and there never more than the fullest chunk
+// fills (a wave without units reads the matrix all the same: a chessboard of 32^3 boxes at 64^3,
+// one unit per chunk, FP64 V-cycle 589 -> 511 us).  No blocks past the fullest chunk (s = 4 at
+// 16^3 x 200, FP64 2430 -> 1477).  Blocks along the rows: until the launch has four blocks per compute
+// unit (64^3 s = 4 FP64 patch products 43 / 40 / 35 / 38 us with one, two, four and eight), or a
+// wave one tile.
 template <typename T, int MODE>
 hipError_t gemm(GemmArgs<T> a, const Bat& bt, hipStream_t st) {
   if (a.nchunks <= 0) return hipSuccess;
@@ -351,8 +353,13 @@ hipError_t gemm(GemmArgs<T> a, const Bat& bt, hipStream_t st) {
   const size_t max_lds = 64 * 1024, lds1 = (size_t)a.npadK * 16 * sizeof(T);
   const int ntiles = a.npadR / 16;
   int nu = ntiles >= 4 ? 1 : (ntiles >= 2 ? 2 : 4);
-  if (chunks >= 256 && nu < 4 && 2 * nu * lds1 <= max_lds) nu *= 2;
-  const int64_t sub = (int64_t)a.nchunks * (4 / nu);
+  const int groups = (a.fill + 15) / 16;
+  if (chunks >= 256) {
+    if (nu < 4 && 2 * nu * lds1 <= max_lds) nu *= 2;
+    while (nu > 1 && nu / 2 >= groups) nu /= 2;
+  }
+  a.nsub = (groups + nu - 1) / nu;
+  const int64_t sub = (int64_t)a.nchunks * a.nsub;
   const int64_t want = (1024 + sub * bt.count - 1) / (sub * bt.count);
   a.nrb = (int)std::max<int64_t>(1, std::min<int64_t>(want, (ntiles + 4 / nu - 1) / (4 / nu)));
   const size_t lds = nu * lds1;

@@ -35,6 +35,8 @@ struct GemmArgs {
   const int64_t* relOut;
   int npadK, npadR;     // multiples of 16
   int nrb;              // blocks along the rows (set by the launch)
+  int nsub;             // blocks along a chunk's units (set by the launch)
+  int fill;             // units of the fullest chunk (at most 64)
   int64_t vlen;         // vector length per pair
   int64_t ylen;         // Y length per pair
   int64_t nunits;       // units of the level (Y is row-major over them: row r of unit u at r * nunits + u)
