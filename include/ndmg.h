@@ -106,8 +106,9 @@ typedef struct ndmg_opts {
                            forms are the Galerkin restrictions of the fine one, and every
                            subdomain and patch gets the factors of its own alphas (any
                            smoother and subdomain size; subdomains of 2 with the vertex
-                           smoother on its own kernels, the others on the gathered
-                           products).  Single problems only (ndmg_setup, or one problem
+                           smoother on its own kernels or, for many small boxes, on the
+                           gathered products, which serve the others).  Single problems
+                           only (ndmg_setup, or one problem
                            in ndmg_setup_batched); bottom_n must be 0; ndmg_export_factor
                            is refused.  ndmg_curlcurl_form then returns lam^T K_c u with
                            K_c = sum_T coef_T K_T, the derivative of A in alpha.          */
