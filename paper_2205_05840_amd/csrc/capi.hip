@@ -190,16 +190,19 @@ int check_opts(const ndmg_opts* o_in, ndmg_opts* o) {
 // type of its own, and, by its fewer launches, while its workgroups stay few.  V-cycles in us,
 // box form / generic, FP32 and FP64 (r boxes per axis, k right-hand sides):
 //   r = 4, 128^3, two materials 421 / 734, 649 / 1065; r = 2, 64^3, k = 4 283 / 422, 371 / 602;
-//   r = 7, 56^3, k = 8, each box its own factor 1074 / 1204, 1980 / 2333; two materials
-//   1051 / 685, 1939 / 970;
+//   r = 7, 56^3, k = 8, each box its own factor 1073 / 1205, 1975 / 1572; two materials
+//   1049 / 687, 1941 / 968;
 //   r = 8, 64^3, every other box (w = 4, 4200 workgroups) 171 / 179, 233 / 210; r = 6, 48^3, two
-//   materials (2621) 142 / 163, 181 / 185; r = 5, 40^3 (1573) 126 / 145, 150 / 150, k = 16 630 /
-//   552, 1075 / 816;
-//   r = 10, 40^3 (w = 2), a rod (597) 89 / 99, 101 / 101, a slab (1347) 96 / 103, 118 / 105, every
-//   other box (8070) 143 / 119, 221 / 127;
-//   r = 7, 14^3 (w = 1), k = 64, two materials (276 types, 1190) 502 / 581, 1085 / 1248, a corner
-//   (20 types, 110) 154 / 124, 210 / 173;
-//   r = 16, 64^3, a corner of 27 boxes 129 / 130, 148 / 146; r = 20, 80^3 168 / 160, 198 / 162.
+//   materials (2621) 142 / 163, 181 / 184; r = 5, 40^3 (1573) 126 / 145, 150 / 150, k = 16 635 /
+//   555, 1075 / 818;
+//   r = 10, 40^3 (w = 2), a rod (597) 89 / 99, 101 / 101, a slab (1347) 97 / 103, 118 / 104, every
+//   other box (8070) 144 / 122, 221 / 122;
+//   r = 7, 14^3 (w = 1), k = 64, two materials (276 types, 1190) 503 / 583, 1087 / 942, a corner
+//   (20 types, 110) 155 / 123, 210 / 153;
+//   r = 16, 64^3, a corner of 27 boxes 131 / 131, 149 / 147; r = 20, 80^3 168 / 161, 198 / 164.
+// Where nearly every triple has its own type, several right-hand sides in FP64 go either way
+// (r = 7, 28^3, k = 8 961 / 664, k = 16 1464 / 1456; r = 5, 20^3, k = 32 872 / 1157; 40^3, k = 16
+// 1086 / 1223): the line serves both precisions.
 // Builds its patches; false (a level that the form cannot hold, too) leaves *out empty.
 bool box_form(const LevelHost& L, const ndmg::CoefBoxes& cf, bool boundary, int count, size_t elem,
               ndmg::BoxPatches* out) {
